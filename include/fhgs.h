@@ -107,8 +107,9 @@ typedef enum { FH_PRIM_GAUSSIAN = 0, FH_PRIM_SURFEL = 1, FH_ENUM_RANGE(FH_PRIM) 
 
 /* Arithmetic form of the compositing kernels. */
 typedef enum {
-    FH_FORM_F32 = 0,        /* FP32 blending; the adjoint and fusion on the FP32 VALU; the forward on MFMA with
-                               three-term BF16 splits of w and f for FP32 features where d allows, else on the VALU */
+    FH_FORM_F32 = 0,        /* FP32 blending; the adjoint and fusion contract FP32 operands on the FP32 matrix unit;
+                               the forward on MFMA with three-term BF16 splits of w and f for FP32 features where d
+                               allows, else on the VALU */
     FH_FORM_BF16 = 1,       /* BF16 features, (pixels x K)(K x D) blends on MFMA, FP32 accumulation */
     FH_ENUM_RANGE(FH_FORM)
 } fh_form;
@@ -158,9 +159,9 @@ typedef struct {
  *              workgroups per tile with twice the registers each, or 4 for
  *              four workgroups per tile, several resident per CU, each with
  *              its own barriers; the FP32 VALU forward: 16).
- *   bwd_chunk  Gaussians per back-to-front chunk of the FP32-form adjoint:
- *              16 or 32 (32 needs d <= 512).  The BF16-form adjoint always
- *              takes 32 (the MFMA k).
+ *   bwd_chunk  16 or 32 (32 needs d <= 512); kept for callers that set it: the
+ *              adjoint of either form walks 32 positions at a time whatever it
+ *              says.
  *   schedule   order in which the MFMA walk kernels take the (view, tile)
  *              work items: 0 tile index order; 1 longest first (tiles sorted
  *              by their list length for the forward, by their traversal

@@ -538,8 +538,7 @@ static void fill_bwd_args(const fh_plan* p, const fh_gaussians* g, void* ws, con
 
 static int visit_sort_passes(const fh_plan* p) { return (p->rank_bits + 7) / 8; }
 
-// The BF16-MFMA backward covers d <= 256; wider features use the FP32-VALU
-// backward with BF16 feature loads.
+// The form's adjoint and fusion kernels.
 static void launch_bwd(const fh_plan* p, void* ws, const BwdArgs& a0, const ViewTable& vt, bool fuse, hipStream_t s) {
     if (p->form == FH_FORM_BF16 && render_bwd_bf16_supported(p->d)) {
         BwdArgs a = a0;
@@ -550,7 +549,7 @@ static void launch_bwd(const fh_plan* p, void* ws, const BwdArgs& a0, const View
         launch_render_bwd_bf16(a, vt, (int)p->n_tiles, a.dC != nullptr, fuse, s);
     } else {
         const BwdArgs& a = a0;
-        launch_render_bwd_f32(a, vt, (int)p->n_tiles, fuse, p->tuning.bwd_chunk, s);
+        launch_render_bwd_f32(a, vt, (int)p->n_tiles, a.dC != nullptr, fuse, s);
     }
 }
 

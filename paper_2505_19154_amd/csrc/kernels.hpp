@@ -165,8 +165,8 @@ void launch_render_bwd_bf16(const BwdArgs& a, const ViewTable& vt, int n_tiles, 
 void launch_visit_stage(const VisitStageArgs& a, int n_tiles, hipStream_t s);
 void launch_vseg(const uint32_t* skeys, const Counters* c, int64_t cap, uint32_t* vseg, hipStream_t s);
 void launch_check_visits(const uint32_t* tile_voff, int n_tiles, Counters* c, int64_t cap, hipStream_t s);
-// chunk: Gaussians per back-to-front chunk (16, or 32 when d <= 512)
-void launch_render_bwd_f32(const BwdArgs& a, const ViewTable& vt, int n_tiles, bool fuse, int chunk, hipStream_t s);
+// render_bwd_f32.hip.  grads: the gradient kernel (needs dC); fuse: the fusion kernel (needs the target)
+void launch_render_bwd_f32(const BwdArgs& a, const ViewTable& vt, int n_tiles, bool grads, bool fuse, hipStream_t s);
 // gp: floats per partial row, 12 (Gaussians: 10 used) or 16 (surfels: 14 used)
 void launch_reduce_geom(const ReduceArgs& a, int gp, hipStream_t s);
 void launch_reduce_fuse(const ReduceArgs& a, hipStream_t s);

@@ -486,9 +486,12 @@ __device__ __forceinline__ void quat_adjoint(const double* qn, double qnorm, con
 __device__ __forceinline__ void colour_adjoint(const ProjectBwdArgs& a, const fh_camera& cam, const float* mu,
                                                const float* shg, int nb, const float* urgb_in, float* gmu,
                                                float (*gsh)[3]) {
-    float cp[3];
-    cam_centre(cam, cp);
-    float ddx = mu[0] - cp[0], ddy = mu[1] - cp[1], ddz = mu[2] - cp[2];
+    // the offset from the camera centre in FP64, rounded once: a component near
+    // zero keeps its relative accuracy, and with it the SH gradient Y_b(dir) urgb
+    double cpd[3];
+    for (int k = 0; k < 3; ++k)
+        cpd[k] = -((double)cam.R[k] * cam.t[0] + (double)cam.R[3 + k] * cam.t[1] + (double)cam.R[6 + k] * cam.t[2]);
+    const float ddx = (float)(mu[0] - cpd[0]), ddy = (float)(mu[1] - cpd[1]), ddz = (float)(mu[2] - cpd[2]);
     const float il = 1.0f / sqrtf(ddx * ddx + ddy * ddy + ddz * ddz);
     const float dx = ddx * il, dy = ddy * il, dz = ddz * il;
     float Y[16];

@@ -129,210 +129,6 @@ __global__ void k_check_visits(const uint32_t* tile_voff, int n_tiles, Counters*
     }
 }
 
-// ---------------------------------------------------------------------------
-
-template <int K, bool FUSE, bool SURF>
-__global__ __launch_bounds__(256) void k_render_bwd_f32(BwdArgs a, ViewTable vt) {
-    using RecT = typename PrimRec<SURF>::T;
-    constexpr int NQ = SURF ? 14 : 10;    // per-instance partial terms
-    constexpr int GP = SURF ? 16 : 12;    // floats per partial row
-    extern __shared__ float dyn[];
-    __shared__ RecT srec[K];
-    __shared__ uint32_t sg[K];
-    __shared__ float sred[4][K][NQ];
-    if (a.counters->inst_overflow || a.counters->visit_overflow) return;
-    const int t = blockIdx.x;
-    const uint32_t nt = a.tile_niter[t];
-    if (nt == 0) return;
-    const int D = a.d;
-    float* sfeat = dyn;                              // [K][D]
-    float* sW = dyn + (size_t)K * (D > 0 ? D : 1);   // [256][K+1]
-    const int v = view_of_tile(vt, t);
-    const int lt = t - vt.tile_off[v];
-    const int tx = lt % vt.tiles_x[v], ty = lt / vt.tiles_x[v];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int px = tx * TILE + (threadIdx.x % TILE), py = ty * TILE + (threadIdx.x / TILE);
-    const bool inside = px < vt.width[v] && py < vt.height[v];
-    const float x = (float)px + 0.5f, y = (float)py + 0.5f;
-    const uint32_t voff = a.tile_voff[t];
-    const int64_t p = vt.pix_off[v] + (int64_t)py * vt.width[v] + px;
-
-    const uint32_t nit = inside ? a.n_iter[p] : 0u;
-    float T = inside ? a.T_final[p] : 1.0f;
-    const float Tfin = T;
-    float dCp[3] = {0, 0, 0};
-    if (inside && a.dC) {
-        dCp[0] = a.dC[3 * p];
-        dCp[1] = a.dC[3 * p + 1];
-        dCp[2] = a.dC[3 * p + 2];
-    }
-    const float dTp = (inside && a.dT) ? a.dT[p] : 0.0f;
-    float S = 0.0f;
-    const float LN2 = 0.69314718055994531f;
-
-    for (int ce = (int)nt; ce > 0; ce -= K) {
-        const int cs = ce - K > 0 ? ce - K : 0;
-        const int cnt = ce - cs;
-        if (threadIdx.x < cnt) {
-            const int64_t vi = (int64_t)voff + cs + threadIdx.x;
-            srec[threadIdx.x] = load_rec<SURF>(a.vrec, vi);
-            sg[threadIdx.x] = a.vgid[vi];
-        }
-        __syncthreads();
-        if (D > 0 && (a.dF || FUSE)) {
-            for (int idx = threadIdx.x; idx < cnt * D; idx += 256) {
-                const int k = idx / D, c = idx - k * D;
-                sfeat[k * D + c] = load_feat(a.feat, a.feat_bf16, (int64_t)sg[k] * D + c);
-            }
-        }
-        __syncthreads();
-        // g_k's feature part: f_k . dF(p)
-        float gacc[K];
-#pragma unroll
-        for (int k = 0; k < K; ++k) gacc[k] = 0.0f;
-        if (a.dF && D > 0 && inside && (uint32_t)cs < nit) {
-            const float* dfp = a.dF + p * D;
-            if ((D & 3) == 0) {
-                for (int c = 0; c < D; c += 4) {
-                    const float4 df = *reinterpret_cast<const float4*>(dfp + c);
-#pragma unroll
-                    for (int k = 0; k < K; ++k)
-                        if (k < cnt) {
-                            const float4 f = *reinterpret_cast<const float4*>(&sfeat[k * D + c]);
-                            gacc[k] += f.x * df.x + f.y * df.y + f.z * df.z + f.w * df.w;
-                        }
-                }
-            } else {
-                for (int c = 0; c < D; ++c) {
-                    const float df = dfp[c];
-#pragma unroll
-                    for (int k = 0; k < K; ++k)
-                        if (k < cnt) gacc[k] += sfeat[k * D + c] * df;
-                }
-            }
-        }
-        // back to front over the chunk
-#pragma unroll
-        for (int k = K - 1; k >= 0; --k) {
-            if (k >= cnt) continue;
-            const int pos = cs + k;
-            float q[NQ];
-#pragma unroll
-            for (int m = 0; m < NQ; ++m) q[m] = 0.0f;
-            float w = 0.0f;
-            bool contrib = false;
-            if (inside && (uint32_t)pos < nit) {
-                const RecT r = srec[k];
-                float alpha, raw;
-                [[maybe_unused]] AlphaEval ae;
-                [[maybe_unused]] SurfEval se;
-                if constexpr (SURF) {
-                    se = eval_surfel(r, x, y);
-                    alpha = se.alpha;
-                    raw = se.raw;
-                } else {
-                    ae = eval_alpha(r, x, y);
-                    alpha = ae.alpha;
-                    raw = ae.raw;
-                }
-                if (alpha >= ALPHA_MIN) {
-                    contrib = true;
-                    const float inv = 1.0f / (1.0f - alpha);
-                    const float Tk = T * inv;
-                    w = alpha * Tk;
-                    const float gk = r.r2.y * dCp[0] + r.r2.z * dCp[1] + r.r2.w * dCp[2] + gacc[k];
-                    const float dalpha = Tk * gk - (S + Tfin * dTp) * inv;
-                    S += w * gk;
-                    T = Tk;
-                    const float dpow = (raw < ALPHA_MAX) ? dalpha * alpha : 0.0f;
-                    if constexpr (SURF) {
-                        // dL/dk = dpow (-u / k2, -v / k2, (u^2 + v^2) / k2), k linear in the record
-                        const float l0 = -dpow * se.u * se.ik2, l1 = -dpow * se.v * se.ik2;
-                        const float l2 = dpow * (se.u * se.u + se.v * se.v) * se.ik2;
-                        const float a0 = r.r1.x, a1 = r.r1.y, b0 = r.r1.z, b1 = r.r1.w;
-                        const float e1 = r.r3.y, e2 = r.r3.z;
-                        q[0] = -(l0 * b1 - l1 * b0 - l2 * e2);
-                        q[1] = -(l1 * a0 - l0 * a1 - l2 * e1);
-                        q[2] = l1 * se.dy;
-                        q[3] = -l0 * se.dy;
-                        q[4] = -l1 * se.dx;
-                        q[5] = l0 * se.dx;
-                        q[6] = l2;
-                        q[7] = -l2 * se.dy;
-                        q[8] = -l2 * se.dx;
-                    } else {
-                        // d power / d(u, v) = Sigma2^-1 d, from the eigenframe:
-                        // Sigma2^-1 d = -2 ln2 (q1 a e1 + q2 b e2), e2 = (-e_y, e_x)
-                        const float ex = r.r1.x, ey = r.r1.y;
-                        const float qa = r.r1.z * ae.a, qb = r.r1.w * ae.b;
-                        const float sdx = -2.0f * LN2 * (qa * ex - qb * ey);
-                        const float sdy = -2.0f * LN2 * (qa * ey + qb * ex);
-                        q[0] = dpow * sdx;
-                        q[1] = dpow * sdy;
-                        q[2] = dpow * (-0.5f * ae.dx * ae.dx);
-                        q[3] = dpow * (-ae.dx * ae.dy);
-                        q[4] = dpow * (-0.5f * ae.dy * ae.dy);
-                    }
-                    q[NQ - 5] = dpow;
-                    q[NQ - 4] = w * dCp[0];
-                    q[NQ - 3] = w * dCp[1];
-                    q[NQ - 2] = w * dCp[2];
-                    q[NQ - 1] = w;
-                }
-            }
-            if (FUSE) sW[threadIdx.x * (K + 1) + k] = w;
-            if (__any(contrib)) {
-#pragma unroll
-                for (int m = 0; m < NQ; ++m) {
-                    const float r = wave_sum(q[m]);
-                    if (lane == 0) sred[wv][k][m] = r;
-                }
-            } else if (lane == 0) {
-#pragma unroll
-                for (int m = 0; m < NQ; ++m) sred[wv][k][m] = 0.0f;
-            }
-        }
-        __syncthreads();
-        for (int idx = threadIdx.x; idx < cnt * GP; idx += 256) {
-            const int k = idx / GP, m = idx - k * GP;
-            const float val = m < NQ ? (sred[0][k][m] + sred[1][k][m]) + (sred[2][k][m] + sred[3][k][m]) : 0.0f;
-            a.part_geom[((int64_t)voff + cs + k) * GP + m] = val;
-        }
-        if (FUSE && D > 0) {
-            // sum_p w(p) target(p) for the chunk's instances; pixels outside the image have w = 0
-            const int W = vt.width[v], H = vt.height[v];
-            for (int c = threadIdx.x; c < D; c += 256) {
-                float acc[K];
-#pragma unroll
-                for (int k = 0; k < K; ++k) acc[k] = 0.0f;
-                // one tile row (16 pixels) of target values in flight at a time
-                for (int row = 0; row < TILE; ++row) {
-                    const int qy = ty * TILE + row;
-                    float tv[TILE];
-#pragma unroll
-                    for (int m = 0; m < TILE; ++m) {
-                        const int qx = tx * TILE + m;
-                        tv[m] = (qx < W && qy < H)
-                                    ? load_feat(a.target, a.target_bf16,
-                                                (vt.pix_off[v] + (int64_t)qy * W + qx) * D + c)
-                                    : 0.0f;
-                    }
-#pragma unroll
-                    for (int m = 0; m < TILE; ++m) {
-                        const int pp = row * TILE + m;
-#pragma unroll
-                        for (int k = 0; k < K; ++k) acc[k] += sW[pp * (K + 1) + k] * tv[m];
-                    }
-                }
-#pragma unroll
-                for (int k = 0; k < K; ++k)
-                    if (k < cnt) a.part_fuse[((int64_t)voff + cs + k) * D + c] = acc[k];
-            }
-        }
-        __syncthreads();
-    }
-}
-
 // Per depth rank j (view v = j / n): the rank of each (view, Gaussian) and the
 // screen records in rank order, so that a tile list entry (a rank) reaches its
 // record with one load.
@@ -394,30 +190,6 @@ void launch_render_fwd_f32(const RenderArgs& a, const ViewTable& vt, int n_tiles
 
 void launch_check_visits(const uint32_t* tile_voff, int n_tiles, Counters* c, int64_t cap, hipStream_t s) {
     hipLaunchKernelGGL(k_check_visits, dim3(1), dim3(64), 0, s, tile_voff, n_tiles, c, cap);
-}
-
-template <int K, bool SURF>
-static void launch_bwd_ks(const BwdArgs& a, const ViewTable& vt, int n_tiles, bool fuse, hipStream_t s) {
-    const size_t dyn = sizeof(float) * ((size_t)K * (a.d > 0 ? a.d : 1) + (fuse ? (size_t)256 * (K + 1) : 0));
-    if (fuse)
-        hipLaunchKernelGGL((k_render_bwd_f32<K, true, SURF>), dim3(n_tiles), dim3(256), dyn, s, a, vt);
-    else
-        hipLaunchKernelGGL((k_render_bwd_f32<K, false, SURF>), dim3(n_tiles), dim3(256), dyn, s, a, vt);
-}
-
-template <int K>
-static void launch_bwd_k(const BwdArgs& a, const ViewTable& vt, int n_tiles, bool fuse, hipStream_t s) {
-    if (a.prim == FH_PRIM_SURFEL)
-        launch_bwd_ks<K, true>(a, vt, n_tiles, fuse, s);
-    else
-        launch_bwd_ks<K, false>(a, vt, n_tiles, fuse, s);
-}
-
-void launch_render_bwd_f32(const BwdArgs& a, const ViewTable& vt, int n_tiles, bool fuse, int chunk, hipStream_t s) {
-    if (chunk == 32 && a.d <= 512)
-        launch_bwd_k<32>(a, vt, n_tiles, fuse, s);
-    else
-        launch_bwd_k<16>(a, vt, n_tiles, fuse, s);
 }
 
 void launch_rank_tables(const uint32_t* order, const float4* rec, int64_t n, int64_t total, uint32_t* rank_of,
