@@ -154,7 +154,8 @@ typedef struct {
  *              it as three BF16 terms): dividing d, and 32, 64, 96 or 128 (BF16 form only) with
  *              fwd_rows 16, 64, 128 or 256 with fwd_rows 8, or 128 or 256
  *              with fwd_rows 4 (BF16 form only).  Other FP32-form widths: 8,
- *              16, 32 or 64.  0 when d == 0.
+ *              16, 32 or 64, kept for callers that set it (that forward takes
+ *              up to 128 channels a workgroup whatever it says).  0 when d == 0.
  *   fwd_rows   pixel rows per forward workgroup (BF16 form: 16, 8 for two
  *              workgroups per tile with twice the registers each, or 4 for
  *              four workgroups per tile, several resident per CU, each with

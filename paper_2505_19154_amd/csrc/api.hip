@@ -494,7 +494,7 @@ fh_status fh_render_fwd(const fh_plan* p, const fh_gaussians* g, void* ws, const
     if (mfma_forward(p->d, p->form, p->feat_dtype, p->primitive))
         launch_render_fwd_bf16(a, vt, (int)p->n_tiles, p->tuning.fwd_slice, p->tuning.fwd_rows, !a.feat_bf16, s);
     else
-        launch_render_fwd_f32(a, vt, (int)p->n_tiles, p->tuning.fwd_slice, s);
+        launch_render_fwd_f32(a, vt, (int)p->n_tiles, s);
     prof_end(FH_K_RENDER_FWD, s);
     uint32_t* voff = buf<uint32_t>(p, ws, WS_TILE_VOFF);
     device_exclusive_scan(tile_niter, voff, p->n_tiles, buf<uint32_t>(p, ws, WS_SCAN_TMP), 1, s);

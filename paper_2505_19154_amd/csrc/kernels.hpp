@@ -152,8 +152,7 @@ struct ReduceArgs {
     float *acc_sum, *acc_comp, *acc_wsum, *acc_wcomp;
     int wslot;                 // per-instance partial row (12 floats, surfels 16): weight sum at entry 9 (surfels 13)
 };
-// slice: channels per workgroup (8, 16, 32 or 64)
-void launch_render_fwd_f32(const RenderArgs& a, const ViewTable& vt, int n_tiles, int slice, hipStream_t s);
+void launch_render_fwd_f32(const RenderArgs& a, const ViewTable& vt, int n_tiles, hipStream_t s);
 // slice: channels per workgroup; rows: pixel rows per workgroup (16 or 8)
 bool render_fwd_bf16_shape_ok(int d, int slice, int rows);
 void launch_render_fwd_bf16(const RenderArgs& a, const ViewTable& vt, int n_tiles, int slice, int rows, bool fsplit,

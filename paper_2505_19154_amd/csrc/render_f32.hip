@@ -1,22 +1,11 @@
-// Front-to-back compositing (FP32 VALU form) and its adjoint.
+// Front-to-back compositing in the FP32 form, for the widths and storage types
+// that the split-BF16 forward (render_bf16.hip) does not take, and small
+// kernels around it.
 //
 // Forward (Section 3.1): for every pixel, walk its tile's depth-sorted list;
 //   alpha = min(0.99, o G), skip if alpha < 1/255, stop before T drops below
 //   1e-4, w = alpha T, C += w rgb, F += w f, T *= (1 - alpha).
-// One 256-thread workgroup per (tile, feature slice); records and feature rows
-// of 256 instances at a time are staged in LDS and read by every pixel.
 //
-// Backward (Appendix A.2): per tile, back to front from the tile's longest
-// traversal, transmittance recovered by division from T_final,
-//   dL/dalpha_k = T_k g_k - (S_k + T_final dT) / (1 - alpha_k),
-//   g_k = rgb_k . dC + f_k . dF,  S_k = sum_{i>k} w_i g_i,
-// reduced over the tile's pixels into per-instance partials (no atomics);
-// optionally the fusion partials sum_p w(p) target(p) in the same sweep.
-//
-// Both kernels also take the surfel primitive (Section 3.1; SURF = true):
-// four-float4 records (see k_project_surfel), the density at the ray-plane
-// intersection, and 14 per-instance partials (the nine record entries' terms,
-// sum dL/dpower, rgb, sum w) in rows of 16 floats.
 #include "kernels.hpp"
 
 namespace fh {
@@ -31,91 +20,279 @@ __device__ __forceinline__ float load_feat(const void* f, int bf16, int64_t idx)
     return bf16 ? bf16_to_f32(static_cast<const uint16_t*>(f)[idx]) : static_cast<const float*>(f)[idx];
 }
 
-template <int DS, bool SURF>
-__global__ __launch_bounds__(256) void k_render_fwd_f32(RenderArgs a, ViewTable vt) {
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// One 256-thread workgroup per (tile, slice of 16 NB channels); wave w owns the
+// pixel rows 4 w .. 4 w + 3, one pixel per lane.  The walk is sequential per
+// pixel (the transmittance is the product in list order); the alphas of eight
+// positions are evaluated ahead of it, so that their latency overlaps.  The
+// weights of 16 positions go to LDS that only this wave reads, and the wave
+// contracts them with the staged features on the FP32 matrix unit,
+//   F[64 px x 16 NB] += W[64 px x 16] . Feat[16 x 16 NB]
+// (v_mfma_f32_16x16x4_f32, FP32 throughout), so a slice of 128 channels walks
+// once where FMAs from LDS took slices of 16 to 64.  Records, Gaussians and
+// features are staged a chunk of 32 positions at a time, requested one to three
+// chunks ahead (as in render_bf16.hip).  Bound: VALU work of the walk (about 30
+// instructions per pixel and position), then the FP32 matrix rate at 256
+// channels.  Against the VALU form: 500k, 1920x1080, D = 256 (BF16 storage)
+// 5.57 -> 2.50 ms; 150k, 987x657, D = 0 123 -> 88 us; 1k, 128x128, D = 16 69 ->
+// 54 us.
+template <int NB, bool SURF>
+__global__ __launch_bounds__(256, 2) void k_render_fwd_f32(RenderArgs a, ViewTable vt, int vec) {
     using RecT = typename PrimRec<SURF>::T;
-    __shared__ RecT srec[256];
-    __shared__ float sfeat[256][DS > 0 ? DS : 1];
-    __shared__ uint32_t smax[4];
+    constexpr int FK = 32;                               // positions per chunk
+    constexpr int DS = 16 * NB;
+    constexpr int FST = DS % 32 == 0 ? DS + 16 : DS;     // feature row stride: lanes q (rows apart) 16 dwords apart mod 64
+    constexpr int WST = 64 + 16;                         // weight row stride, the same
+    constexpr int GE = 4;                                // positions evaluated ahead of the walk
+    constexpr int NG = NB > 0 ? 4 * NB : 1;              // four-channel items per feature row
+    constexpr int ITEMS = NB > 0 ? FK * NG : 0, NI = NB > 0 ? (ITEMS + 255) / 256 : 1;
+    __shared__ RecT srec[3][FK];
+    __shared__ uint32_t sg[3][FK];
+    __shared__ __attribute__((aligned(16))) float sft[NB > 0 ? 2 * FK * FST : 4];
+    __shared__ float sw[NB > 0 ? 4 * 16 * WST : 4];
+    __shared__ uint32_t smax[4], sodd;
+    __shared__ uint8_t sbusy[2][4];
     if (a.counters->inst_overflow) return;
     const int t = blockIdx.x, slice = blockIdx.y, d0 = slice * DS;
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int q = lane >> 4, xi = lane & 15;
     const int v = view_of_tile(vt, t);
     const int lt = t - vt.tile_off[v];
     const int tx = lt % vt.tiles_x[v], ty = lt / vt.tiles_x[v];
-    const int px = tx * TILE + (threadIdx.x % TILE), py = ty * TILE + (threadIdx.x / TILE);
+    const int px = tx * TILE + xi, py = ty * TILE + 4 * w + q;
     const bool inside = px < vt.width[v] && py < vt.height[v];
     const float x = (float)px + 0.5f, y = (float)py + 0.5f;
-    const uint32_t s = a.ranges[2 * t], e = a.ranges[2 * t + 1];
-    const int ds_here = (a.d - d0) < DS ? (a.d - d0) : DS;
+    const uint32_t s = a.ranges[2 * t], len = a.ranges[2 * t + 1] - s;
+    const int k = (int)threadIdx.x;   // list position within a chunk (threads 0..FK-1)
 
-    float T = 1.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f;
-    float F[DS > 0 ? DS : 1];
+    auto rank_at = [&](uint32_t pos) { return pos < len ? inst_rank(a.keys, a.vals, (int64_t)s + pos, a.rank_bits, a.packed) : 0u; };
+    auto get_rec = [&](uint32_t j, RecT& r, uint32_t& g) {
+        r = load_rec<SURF>(a.rrec, j);
+        g = a.order[j];
+    };
+    auto put_rec = [&](int buf, uint32_t pos, const RecT& r, uint32_t g) {
+        const bool real = pos < len;
+        srec[buf][k] = real ? r : pad_rec<SURF>();   // padding: opacity 0 never blends
+        sg[buf][k] = real ? g : 0xFFFFFFFFu;
+    };
+    auto load_feats = [&](const uint32_t* gl, float4* fr) {
 #pragma unroll
-    for (int c = 0; c < (DS > 0 ? DS : 1); ++c) F[c] = 0.0f;
-    bool done = !inside;
-    uint32_t last = 0;
-
-    for (uint32_t base = s; base < e; base += 256) {
-        const uint32_t cnt = (e - base) < 256u ? (e - base) : 256u;
-        if (threadIdx.x < cnt) {
-            const int64_t i = base + threadIdx.x;
-            const uint32_t j = inst_rank(a.keys, a.vals, i, a.rank_bits, a.packed);
-            const uint32_t g = a.order[j];
-            srec[threadIdx.x] = load_rec<SURF>(a.rrec, j);
-            if (DS > 0) {
-#pragma unroll
-                for (int c = 0; c < DS; ++c)
-                    sfeat[threadIdx.x][c] = c < ds_here ? load_feat(a.feat, a.feat_bf16, (int64_t)g * a.d + d0 + c) : 0.0f;
-            }
-        }
-        __syncthreads();
-        if (!done) {
-            for (uint32_t k = 0; k < cnt; ++k) {
-                const RecT r = srec[k];
-                const float alpha = prim_alpha<SURF>(r, x, y);
-                if (alpha < ALPHA_MIN) continue;
-                const float Tn = T * (1.0f - alpha);
-                if (Tn < T_MIN) {
-                    done = true;
-                    break;
+        for (int it = 0; it < NI; ++it) {
+            const int idx = (int)threadIdx.x + 256 * it;
+            fr[it] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (idx < ITEMS) {
+                const uint32_t g = gl[idx / NG];
+                const int c = d0 + 4 * (idx % NG);
+                if (g != 0xFFFFFFFFu) {
+                    if (a.feat_bf16) {
+                        const uint16_t* f = static_cast<const uint16_t*>(a.feat) + (int64_t)g * a.d;
+                        if (vec) {
+                            if (c < a.d) {
+                                const uint2 u = *reinterpret_cast<const uint2*>(f + c);
+                                fr[it] = make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xFFFF0000u),
+                                                     __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xFFFF0000u));
+                            }
+                        } else {
+                            fr[it] = make_float4(c < a.d ? bf16_to_f32(f[c]) : 0.f, c + 1 < a.d ? bf16_to_f32(f[c + 1]) : 0.f,
+                                                 c + 2 < a.d ? bf16_to_f32(f[c + 2]) : 0.f,
+                                                 c + 3 < a.d ? bf16_to_f32(f[c + 3]) : 0.f);
+                        }
+                    } else {
+                        const float* f = static_cast<const float*>(a.feat) + (int64_t)g * a.d;
+                        if (vec) {
+                            if (c < a.d) fr[it] = *reinterpret_cast<const float4*>(f + c);
+                        } else {
+                            fr[it] = make_float4(c < a.d ? f[c] : 0.f, c + 1 < a.d ? f[c + 1] : 0.f,
+                                                 c + 2 < a.d ? f[c + 2] : 0.f, c + 3 < a.d ? f[c + 3] : 0.f);
+                        }
+                    }
                 }
-                const float w = alpha * T;
-                c0 += w * r.r2.y;
-                c1 += w * r.r2.z;
-                c2 += w * r.r2.w;
-#pragma unroll
-                for (int c = 0; c < DS; ++c) F[c] += w * sfeat[k][c];
-                T = Tn;
-                last = base - s + k + 1;
             }
         }
-        if (__syncthreads_count(!done) == 0) break;
+    };
+    // (a feature that is not finite enters the contraction as zero, 0 * inf must
+    // not reach the pixels that do not blend it, and is added at the end)
+    auto store_feats = [&](const float4* fr, int buf) {
+#pragma unroll
+        for (int it = 0; it < NI; ++it) {
+            const int idx = (int)threadIdx.x + 256 * it;
+            if (idx < ITEMS) {
+                float4 f = fr[it];
+                if (!(isfinite(f.x) && isfinite(f.y) && isfinite(f.z) && isfinite(f.w))) {
+                    sodd = 1u;
+                    f.x = isfinite(f.x) ? f.x : 0.0f;
+                    f.y = isfinite(f.y) ? f.y : 0.0f;
+                    f.z = isfinite(f.z) ? f.z : 0.0f;
+                    f.w = isfinite(f.w) ? f.w : 0.0f;
+                }
+                *reinterpret_cast<float4*>(&sft[buf * FK * FST + (idx / NG) * FST + 4 * (idx % NG)]) = f;
+            }
+        }
+    };
+
+    // prologue: chunks 0 and 1 into LDS, chunk 2's ranks into registers, then chunk 0's features
+    uint32_t rk2 = 0u;
+    if (threadIdx.x == 0) sodd = 0u;
+    if (threadIdx.x < 8) reinterpret_cast<uint8_t*>(sbusy)[threadIdx.x] = 0;
+    if (k < FK && len > 0) {
+        RecT r0, r1;
+        uint32_t g0, g1;
+        const uint32_t j0 = rank_at((uint32_t)k), j1 = rank_at((uint32_t)(FK + k));
+        rk2 = rank_at((uint32_t)(2 * FK + k));
+        get_rec(j0, r0, g0);
+        get_rec(j1, r1, g1);
+        put_rec(0, (uint32_t)k, r0, g0);
+        put_rec(1, (uint32_t)(FK + k), r1, g1);
+    }
+    __syncthreads();
+    if (NB > 0 && len > 0) {
+        float4 fr[NI];
+        load_feats(sg[0], fr);
+        store_feats(fr, 0);
+    }
+    __syncthreads();
+
+    f32x4 acc[4][NB > 0 ? NB : 1];
+#pragma unroll
+    for (int pb = 0; pb < 4; ++pb)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[pb][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float T = 1.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f;
+    bool done = !inside, wave_done = ballot64(inside) == 0;
+    uint32_t last = 0;
+    float* wsw = sw + w * 16 * WST;
+
+    int b3 = 0, b2 = 0;   // chunk index mod 3 and mod 2
+    for (uint32_t cpos = 0; cpos < len; cpos += FK) {
+        const int n3 = b3 == 2 ? 0 : b3 + 1, nn3 = n3 == 2 ? 0 : n3 + 1;
+        RecT r2;
+        uint32_t g2 = 0u, rk3 = 0u;
+        if (k < FK) {
+            get_rec(rk2, r2, g2);
+            rk3 = rank_at(cpos + (uint32_t)(3 * FK + k));
+        }
+        float4 fr[NI];
+        if constexpr (NB > 0) load_feats(sg[n3], fr);
+
+        if (!wave_done) {
+#pragma unroll 1
+            for (int half = 0; half < 2; ++half) {
+#pragma unroll 1
+                for (int grp = 0; grp < 16; grp += GE) {
+                    const RecT* rp = srec[b3] + 16 * half + grp;
+                    float al[GE];
+#pragma unroll
+                    for (int m = 0; m < GE; ++m) al[m] = prim_alpha<SURF>(rp[m], x, y);
+                    asm volatile("" ::: "memory");   // (the colours are read again, not held from above)
+#pragma unroll
+                    for (int m = 0; m < GE; ++m) {
+                        const float4 col = rp[m].r2;   // (opacity, r, g, b)
+                        const float Tn = T * (1.0f - al[m]);
+                        const bool act = !done && !(al[m] < ALPHA_MIN);
+                        const bool stop = act && Tn < T_MIN;
+                        const bool blend = act && !stop;
+                        const float wv = blend ? al[m] * T : 0.0f;
+                        if (blend) {
+                            c0 = __builtin_fmaf(wv, col.y, c0);
+                            c1 = __builtin_fmaf(wv, col.z, c1);
+                            c2 = __builtin_fmaf(wv, col.w, c2);
+                        }
+                        T = blend ? Tn : T;
+                        last = blend ? cpos + (uint32_t)(16 * half + grp + m + 1) : last;
+                        done = done || stop;
+                        if constexpr (NB > 0) wsw[(grp + m) * WST + lane] = wv;
+                    }
+                }
+                if constexpr (NB > 0) {
+                    const float* sf = sft + b2 * FK * FST + 16 * half * FST;
+#pragma unroll
+                    for (int st = 0; st < 4; ++st) {
+                        float aw[4];
+#pragma unroll
+                        for (int pb = 0; pb < 4; ++pb) aw[pb] = wsw[(4 * st + q) * WST + 16 * pb + xi];
+#pragma unroll
+                        for (int j = 0; j < NB; ++j) {
+                            const float f = sf[(4 * st + q) * FST + 16 * j + xi];
+#pragma unroll
+                            for (int pb = 0; pb < 4; ++pb)
+                                acc[pb][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(aw[pb], f, acc[pb][j], 0, 0, 0);
+                        }
+                    }
+                }
+            }
+            wave_done = ballot64(!done) == 0;
+        }
+        // chunk c+1's features and chunk c+2's records to LDS
+        if constexpr (NB > 0) store_feats(fr, b2 ^ 1);
+        if (k < FK) {
+            put_rec(nn3, cpos + (uint32_t)(2 * FK + k), r2, g2);
+            rk2 = rk3;
+        }
+        // leave when every pixel has stopped (flags double-buffered by chunk parity)
+        if (lane == 0) sbusy[b2][w] = wave_done ? 0 : 1;
+        __syncthreads();
+        if (*reinterpret_cast<const uint32_t*>(sbusy[b2]) == 0u) break;
+        b3 = n3;
+        b2 ^= 1;
     }
 
-    const int64_t p = vt.pix_off[v] + (int64_t)py * vt.width[v] + px;
-    if (inside) {
-        if (slice == 0) {
-            a.C[3 * p] = c0;
-            a.C[3 * p + 1] = c1;
-            a.C[3 * p + 2] = c2;
-            a.T[p] = T;
-            a.n_iter[p] = last;
-        }
-        if (DS > 0) {
+    const int64_t rowp = vt.pix_off[v];
+    if (inside && slice == 0) {
+        const int64_t p = rowp + (int64_t)py * vt.width[v] + px;
+        a.C[3 * p] = c0;
+        a.C[3 * p + 1] = c1;
+        a.C[3 * p + 2] = c2;
+        a.T[p] = T;
+        a.n_iter[p] = last;
+    }
+    // F: lane holds F[pixel 4 q + r of row 4 w + pb][channel 16 j + xi]
+    if constexpr (NB > 0) {
 #pragma unroll
-            for (int c = 0; c < DS; ++c)
-                if (c < ds_here) a.F[p * a.d + d0 + c] = F[c];
+        for (int pb = 0; pb < 4; ++pb) {
+            const int fy = ty * TILE + 4 * w + pb;
+            if (fy < vt.height[v]) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int fx = tx * TILE + 4 * q + r;
+                    if (fx < vt.width[v]) {
+                        float* fo = a.F + (rowp + (int64_t)fy * vt.width[v] + fx) * a.d + d0 + xi;
+#pragma unroll
+                        for (int j = 0; j < NB; ++j)
+                            if (d0 + 16 * j + xi < a.d) fo[16 * j] = acc[pb][j][r];
+                    }
+                }
+            }
+        }
+    }
+    if constexpr (NB > 0) {
+        // features that are not finite, added to the pixels that blend them by a
+        // second walk (rare: nothing to do for finite features)
+        __syncthreads();
+        if (sodd != 0u) {
+            __threadfence();   // (this pixel's F was stored by other lanes)
+            __syncthreads();
+            float Tw = 1.0f;
+            for (uint32_t pos = 0; pos < last; ++pos) {
+                const uint32_t j = inst_rank(a.keys, a.vals, (int64_t)s + pos, a.rank_bits, a.packed);
+                const float alpha = prim_alpha<SURF>(load_rec<SURF>(a.rrec, j), x, y);
+                if (alpha < ALPHA_MIN) continue;
+                const float wv = alpha * Tw;
+                Tw = Tw * (1.0f - alpha);
+                const int64_t g = a.order[j];
+                float* fo = a.F + (rowp + (int64_t)py * vt.width[v] + px) * a.d;
+                for (int c = d0; c < a.d && c < d0 + DS; ++c) {
+                    const float f = load_feat(a.feat, a.feat_bf16, g * a.d + c);
+                    if (!isfinite(f)) fo[c] += wv * f;
+                }
+            }
         }
     }
     if (slice == 0) {
         const uint32_t m = wave_max_u32(last);
-        if ((threadIdx.x & 63) == 0) smax[threadIdx.x / 64] = m;
+        if (lane == 0) smax[w] = m;
         __syncthreads();
-        if (threadIdx.x == 0) {
-            uint32_t mm = smax[0];
-            for (int k = 1; k < 4; ++k) mm = smax[k] > mm ? smax[k] : mm;
-            a.tile_niter[t] = mm;
-        }
+        if (threadIdx.x == 0) a.tile_niter[t] = max(max(smax[0], smax[1]), max(smax[2], smax[3]));
     }
 }
 
@@ -167,25 +344,27 @@ __global__ __launch_bounds__(256) void k_fuse_finalize(const float* sum, const f
 
 // ---------------------------------------------------------------------------
 template <bool SURF>
-static void launch_fwd_f32(const RenderArgs& a, const ViewTable& vt, int n_tiles, int slice, hipStream_t s) {
-    if (a.d == 0) {
-        hipLaunchKernelGGL((k_render_fwd_f32<0, SURF>), dim3(n_tiles, 1), dim3(256), 0, s, a, vt);
-        return;
-    }
-    const unsigned ns = (unsigned)((a.d + slice - 1) / slice);
-    switch (slice) {
-        case 8: hipLaunchKernelGGL((k_render_fwd_f32<8, SURF>), dim3(n_tiles, ns), dim3(256), 0, s, a, vt); break;
-        case 16: hipLaunchKernelGGL((k_render_fwd_f32<16, SURF>), dim3(n_tiles, ns), dim3(256), 0, s, a, vt); break;
-        case 32: hipLaunchKernelGGL((k_render_fwd_f32<32, SURF>), dim3(n_tiles, ns), dim3(256), 0, s, a, vt); break;
-        default: hipLaunchKernelGGL((k_render_fwd_f32<64, SURF>), dim3(n_tiles, ns), dim3(256), 0, s, a, vt); break;
-    }
+static void launch_fwd_f32(const RenderArgs& a, const ViewTable& vt, int n_tiles, hipStream_t s) {
+    // 16-byte (BF16: 8-byte) feature loads where every row is aligned to them
+    const int vec = a.d % 4 == 0 && reinterpret_cast<uintptr_t>(a.feat) % (a.feat_bf16 ? 8 : 16) == 0;
+    const unsigned ns = (unsigned)((a.d + 127) / 128);
+    if (a.d == 0)
+        hipLaunchKernelGGL((k_render_fwd_f32<0, SURF>), dim3(n_tiles, 1), dim3(256), 0, s, a, vt, vec);
+    else if (a.d <= 16)
+        hipLaunchKernelGGL((k_render_fwd_f32<1, SURF>), dim3(n_tiles, 1), dim3(256), 0, s, a, vt, vec);
+    else if (a.d <= 32)
+        hipLaunchKernelGGL((k_render_fwd_f32<2, SURF>), dim3(n_tiles, 1), dim3(256), 0, s, a, vt, vec);
+    else if (a.d <= 64)
+        hipLaunchKernelGGL((k_render_fwd_f32<4, SURF>), dim3(n_tiles, 1), dim3(256), 0, s, a, vt, vec);
+    else
+        hipLaunchKernelGGL((k_render_fwd_f32<8, SURF>), dim3(n_tiles, ns), dim3(256), 0, s, a, vt, vec);
 }
 
-void launch_render_fwd_f32(const RenderArgs& a, const ViewTable& vt, int n_tiles, int slice, hipStream_t s) {
+void launch_render_fwd_f32(const RenderArgs& a, const ViewTable& vt, int n_tiles, hipStream_t s) {
     if (a.prim == FH_PRIM_SURFEL)
-        launch_fwd_f32<true>(a, vt, n_tiles, slice, s);
+        launch_fwd_f32<true>(a, vt, n_tiles, s);
     else
-        launch_fwd_f32<false>(a, vt, n_tiles, slice, s);
+        launch_fwd_f32<false>(a, vt, n_tiles, s);
 }
 
 void launch_check_visits(const uint32_t* tile_voff, int n_tiles, Counters* c, int64_t cap, hipStream_t s) {
