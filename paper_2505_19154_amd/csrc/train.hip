@@ -148,114 +148,134 @@ __device__ __forceinline__ void quat_rot(const float* q, float R[9]) {
     R[8] = 1.0f - 2.0f * (x * x + y * y);
 }
 
-struct ParamSet {
-    float *means, *log_scales, *quats, *logit, *sh;
+// Where every parent's rows go: the kept original (or first child) at
+// keep_off[g], the clone or second child at n_keep + extra_off[g].
+struct DensifyMap {
+    int64_t n, n_keep;
+    const uint32_t *action, *keep_off, *extra_off, *keep;
 };
 struct DensifyApplyArgs {
-    int64_t n, n_keep;
-    int nsh;                    // SH floats per Gaussian
-    const uint32_t *action, *keep_off, *extra_off, *keep;
-    ParamSet in, m_in, v_in;    // (const in use)
+    DensifyMap map;
+    const float *means, *log_scales, *quats, *logit;
     const float* z;             // [n, 2, 3] standard normal draws (used by split Gaussians)
-    ParamSet out, m_out, v_out;
-    float *scales_out, *opacity_out;
+    float *means_out, *log_scales_out, *logit_out, *scales_out, *opacity_out;
 };
 
-__device__ __forceinline__ void copy_row(float* dst, const float* src, int k) {
-    for (int i = 0; i < k; ++i) dst[i] = src[i];
-}
-__device__ __forceinline__ void zero_row(float* dst, int k) {
-    for (int i = 0; i < k; ++i) dst[i] = 0.0f;
-}
-
-// One thread per parent: the kept original (or first child) at keep_off[g],
-// the clone or second child at n_keep + extra_off[g].  Split children: means
-// mu + R(q) diag(s) z_j, log-scales log s - ln 1.6, other parameters copied.
-// Moments: a kept original keeps its own, split parents and new Gaussians start
-// at zero.
+// One thread per parent, the values densification computes: split children's
+// means mu + R(q) diag(s) z_j and log-scales log s - ln 1.6, and the activated
+// scales and opacity of every copy.  (Rows that are only copied, quaternions,
+// SH, moments and features, go through k_densify_rows.)
 __global__ __launch_bounds__(TB) void k_densify_apply(DensifyApplyArgs a) {
     const int64_t g = (int64_t)blockIdx.x * TB + threadIdx.x;
-    if (g >= a.n || !a.keep[g]) return;
-    const uint32_t act = a.action[g];
-    const int64_t dst[2] = {(int64_t)a.keep_off[g], a.n_keep + (int64_t)a.extra_off[g]};
+    if (g >= a.map.n || !a.map.keep[g]) return;
+    const uint32_t act = a.map.action[g];
+    const int64_t dst[2] = {(int64_t)a.map.keep_off[g], a.map.n_keep + (int64_t)a.map.extra_off[g]};
     const int ncopy = act != 0u ? 2 : 1;
-    const float* mu = a.in.means + 3 * g;
-    const float* ls = a.in.log_scales + 3 * g;
-    const float* q = a.in.quats + 4 * g;
-    float child[2][3];
-    float lsc[3];
+    const float mu[3] = {a.means[3 * g], a.means[3 * g + 1], a.means[3 * g + 2]};
+    float ls[3] = {a.log_scales[3 * g], a.log_scales[3 * g + 1], a.log_scales[3 * g + 2]};
+    float mean[2][3];
+    for (int j = 0; j < 2; ++j)
+        for (int r = 0; r < 3; ++r) mean[j][r] = mu[r];
     if (act == 2u) {
         float R[9];
+        const float q[4] = {a.quats[4 * g], a.quats[4 * g + 1], a.quats[4 * g + 2], a.quats[4 * g + 3]};
         quat_rot(q, R);
         const float s[3] = {expf(ls[0]), expf(ls[1]), expf(ls[2])};
         for (int j = 0; j < 2; ++j) {
             const float* zj = a.z + 6 * g + 3 * j;
             const float t[3] = {s[0] * zj[0], s[1] * zj[1], s[2] * zj[2]};
             for (int r = 0; r < 3; ++r)
-                child[j][r] = mu[r] + (R[3 * r] * t[0] + R[3 * r + 1] * t[1] + R[3 * r + 2] * t[2]);
+                mean[j][r] = mu[r] + (R[3 * r] * t[0] + R[3 * r + 1] * t[1] + R[3 * r + 2] * t[2]);
         }
         const float ln16 = 0.47000362924573558f;   // ln 1.6
-        for (int r = 0; r < 3; ++r) lsc[r] = ls[r] - ln16;
+        for (int r = 0; r < 3; ++r) ls[r] = ls[r] - ln16;
     }
+    const float logit = a.logit[g], op = 1.0f / (1.0f + expf(-logit));
+    const float sc[3] = {expf(ls[0]), expf(ls[1]), expf(ls[2])};
     for (int c = 0; c < ncopy; ++c) {
         const int64_t o = dst[c];
-        if (act == 2u) {
-            copy_row(a.out.means + 3 * o, child[c], 3);
-            copy_row(a.out.log_scales + 3 * o, lsc, 3);
-        } else {
-            copy_row(a.out.means + 3 * o, mu, 3);
-            copy_row(a.out.log_scales + 3 * o, ls, 3);
+        for (int r = 0; r < 3; ++r) {
+            a.means_out[3 * o + r] = mean[c][r];
+            a.log_scales_out[3 * o + r] = ls[r];
+            a.scales_out[3 * o + r] = sc[r];
         }
-        copy_row(a.out.quats + 4 * o, q, 4);
-        a.out.logit[o] = a.in.logit[g];
-        copy_row(a.out.sh + (int64_t)a.nsh * o, a.in.sh + (int64_t)a.nsh * g, a.nsh);
-        const float* lso = a.out.log_scales + 3 * o;
-        for (int r = 0; r < 3; ++r) a.scales_out[3 * o + r] = expf(lso[r]);
-        a.opacity_out[o] = 1.0f / (1.0f + expf(-a.in.logit[g]));
-        const ParamSet* ms[2] = {&a.m_out, &a.v_out};
-        const ParamSet* mi[2] = {&a.m_in, &a.v_in};
-        for (int k = 0; k < 2; ++k) {
-            const ParamSet& d = *ms[k];
-            if (c == 0 && act != 2u) {
-                const ParamSet& sI = *mi[k];
-                copy_row(d.means + 3 * o, sI.means + 3 * g, 3);
-                copy_row(d.log_scales + 3 * o, sI.log_scales + 3 * g, 3);
-                copy_row(d.quats + 4 * o, sI.quats + 4 * g, 4);
-                d.logit[o] = sI.logit[g];
-                copy_row(d.sh + (int64_t)a.nsh * o, sI.sh + (int64_t)a.nsh * g, a.nsh);
-            } else {
-                zero_row(d.means + 3 * o, 3);
-                zero_row(d.log_scales + 3 * o, 3);
-                zero_row(d.quats + 4 * o, 4);
-                d.logit[o] = 0.0f;
-                zero_row(d.sh + (int64_t)a.nsh * o, a.nsh);
-            }
-        }
+        a.logit_out[o] = logit;
+        a.opacity_out[o] = op;
     }
 }
 
-// Rows of any other per-Gaussian attribute (the frozen features): the same
-// positions as k_densify_apply, every copy the parent's row.  16-byte units
-// when the row allows, else bytes.
-__global__ __launch_bounds__(TB) void k_densify_copy_rows(int64_t n, int64_t n_keep, const uint32_t* __restrict__ action,
-                                                          const uint32_t* __restrict__ keep,
-                                                          const uint32_t* __restrict__ keep_off,
-                                                          const uint32_t* __restrict__ extra_off,
-                                                          const uint8_t* __restrict__ in, uint8_t* __restrict__ out,
-                                                          int64_t row_bytes) {
-    const int64_t g = (int64_t)blockIdx.x * TB + threadIdx.x;
-    if (g >= n || !keep[g]) return;
-    const int64_t dst[2] = {(int64_t)keep_off[g], n_keep + (int64_t)extra_off[g]};
-    const int ncopy = action[g] != 0u ? 2 : 1;
-    for (int c = 0; c < ncopy; ++c) {
-        if (row_bytes % 16 == 0) {
-            const uint4* s4 = reinterpret_cast<const uint4*>(in + g * row_bytes);
-            uint4* d4 = reinterpret_cast<uint4*>(out + dst[c] * row_bytes);
-            for (int64_t i = 0; i < row_bytes / 16; ++i) d4[i] = s4[i];
-        } else {
-            for (int64_t i = 0; i < row_bytes; ++i) out[dst[c] * row_bytes + i] = in[g * row_bytes + i];
+// Rows of per-Gaussian arrays carried to the densified set.  A job is one
+// array: rows of `units` elements (16, 4 or 1 bytes each, as its row size and
+// addresses allow); zero_new: an Adam moment, kept by an original that was not
+// split and zero for every other copy.  A workgroup takes 64 parents and its
+// threads run over (parent, element), so that neighbouring threads move
+// neighbouring elements of a row (370 us for 1.3 GB at 500k Gaussians with 512-byte
+// features, 3.5 TB/s; one thread per parent, which stepped through
+// its rows alone, took 1.98 ms; bound: HBM).
+struct RowJob {
+    const uint8_t* in;
+    uint8_t* out;
+    int64_t units;
+    int unit_bytes;
+    int zero_new;
+};
+constexpr int MAX_ROW_JOBS = 12;
+struct RowJobs {
+    RowJob job[MAX_ROW_JOBS];
+    DensifyMap map;
+};
+constexpr int ROW_PARENTS = 64;
+
+template <typename T>
+__device__ __forceinline__ void densify_rows(const RowJob& J, const uint32_t* d0, const uint32_t* d1, const uint8_t* how,
+                                             int64_t g0, int parents, int64_t n_keep) {
+    const T* in = reinterpret_cast<const T*>(J.in) + g0 * J.units;
+    T* out = reinterpret_cast<T*>(J.out);
+    const T zero = {};
+    if (J.units >= 4 * TB) {
+        // long rows: one at a time, the workgroup over its elements
+        for (int k = 0; k < parents; ++k) {
+            const uint8_t h = how[k];
+            if (!(h & 1)) continue;
+            for (int64_t i = threadIdx.x; i < J.units; i += TB) {
+                const T val = in[k * J.units + i];
+                out[(int64_t)d0[k] * J.units + i] = (J.zero_new && (h & 4)) ? zero : val;
+                if (h & 2) out[(n_keep + (int64_t)d1[k]) * J.units + i] = J.zero_new ? zero : val;
+            }
         }
+        return;
     }
+    const uint32_t U = (uint32_t)J.units, total = (uint32_t)parents * U;
+    for (uint32_t idx = threadIdx.x; idx < total; idx += TB) {
+        const uint32_t k = idx / U, i = idx - k * U;
+        const uint8_t h = how[k];
+        if (!(h & 1)) continue;                       // pruned
+        const T val = in[idx];
+        out[(int64_t)d0[k] * U + i] = (J.zero_new && (h & 4)) ? zero : val;
+        if (h & 2) out[(n_keep + (int64_t)d1[k]) * U + i] = J.zero_new ? zero : val;
+    }
+}
+
+__global__ __launch_bounds__(TB) void k_densify_rows(RowJobs a) {
+    __shared__ uint32_t d0[ROW_PARENTS], d1[ROW_PARENTS];
+    __shared__ uint8_t how[ROW_PARENTS];              // bit 0 kept, 1 copied, 2 split
+    const int64_t g0 = (int64_t)blockIdx.x * ROW_PARENTS;
+    const int parents = (int)(a.map.n - g0 < ROW_PARENTS ? a.map.n - g0 : ROW_PARENTS);
+    if ((int)threadIdx.x < parents) {
+        const int64_t g = g0 + threadIdx.x;
+        const uint32_t act = a.map.action[g];
+        d0[threadIdx.x] = a.map.keep_off[g];
+        d1[threadIdx.x] = a.map.extra_off[g];
+        how[threadIdx.x] = a.map.keep[g] ? (uint8_t)(1u | (act != 0u ? 2u : 0u) | (act == 2u ? 4u : 0u)) : 0;
+    }
+    __syncthreads();
+    const RowJob& J = a.job[blockIdx.y];
+    if (J.unit_bytes == 16)
+        densify_rows<uint4>(J, d0, d1, how, g0, parents, a.map.n_keep);
+    else if (J.unit_bytes == 4)
+        densify_rows<uint32_t>(J, d0, d1, how, g0, parents, a.map.n_keep);
+    else
+        densify_rows<uint8_t>(J, d0, d1, how, g0, parents, a.map.n_keep);
 }
 
 // ---------------------------------------------------------------------------
@@ -264,6 +284,7 @@ __global__ __launch_bounds__(TB) void k_densify_copy_rows(int64_t n, int64_t n_k
 // [b * LOSS_CHUNK, (b + 1) * LOSS_CHUNK) by a fixed tree; one block then adds
 // the partials in block order.
 constexpr int LOSS_CHUNK = 8192;
+constexpr int LOSS_TB = 1024;   // eight elements a thread
 
 __device__ __forceinline__ float block_sum_256(float v, float* sh) {
     v = wave_sum(v);
@@ -276,20 +297,47 @@ __device__ __forceinline__ float block_sum_256(float v, float* sh) {
     return t;
 }
 
-__global__ __launch_bounds__(TB) void k_loss_partial(const float* __restrict__ C, const float* __restrict__ Ct,
-                                                     int64_t count, float scale, float* __restrict__ dC,
-                                                     float* __restrict__ part) {
-    __shared__ float sh[4];
+// One pass, 1024 threads a chunk with two 16-byte loads of each map in flight
+// (256 threads stepping through 32 scalar elements: 26 us at 1297x841 and
+// 18 at 987x657, latency-bound at one block a CU).  vec: every map 16-byte
+// aligned; else, and at the end of the maps, element by element.
+__global__ __launch_bounds__(LOSS_TB) void k_loss_partial(const float* __restrict__ C, const float* __restrict__ Ct,
+                                                          int64_t count, float scale, float* __restrict__ dC,
+                                                          float* __restrict__ part, int vec) {
+    __shared__ float sh[LOSS_TB / 64];
     const int64_t b0 = (int64_t)blockIdx.x * LOSS_CHUNK;
-    const int64_t b1 = b0 + LOSS_CHUNK < count ? b0 + LOSS_CHUNK : count;
+    const float s2 = 2.0f * scale;
     float acc = 0.0f;
-    for (int64_t i = b0 + threadIdx.x; i < b1; i += TB) {
-        const float e = C[i] - Ct[i];
-        acc += e * e;
-        dC[i] = (2.0f * scale) * e;
+    if (vec && b0 + LOSS_CHUNK <= count) {
+        float4 c[2], t[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int64_t i = b0 / 4 + threadIdx.x + LOSS_TB * k;
+            c[k] = reinterpret_cast<const float4*>(C)[i];
+            t[k] = reinterpret_cast<const float4*>(Ct)[i];
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const float4 e = make_float4(c[k].x - t[k].x, c[k].y - t[k].y, c[k].z - t[k].z, c[k].w - t[k].w);
+            acc += (e.x * e.x + e.y * e.y) + (e.z * e.z + e.w * e.w);
+            reinterpret_cast<float4*>(dC)[b0 / 4 + threadIdx.x + LOSS_TB * k] =
+                make_float4(s2 * e.x, s2 * e.y, s2 * e.z, s2 * e.w);
+        }
+    } else {
+        for (int64_t i = b0 + threadIdx.x; i < count && i < b0 + LOSS_CHUNK; i += LOSS_TB) {
+            const float e = C[i] - Ct[i];
+            acc += e * e;
+            dC[i] = s2 * e;
+        }
     }
-    const float t = block_sum_256(acc, sh);
-    if (threadIdx.x == 0) part[blockIdx.x] = t;
+    acc = wave_sum(acc);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float t = 0.0f;
+        for (int k = 0; k < LOSS_TB / 64; ++k) t += sh[k];
+        part[blockIdx.x] = t;
+    }
 }
 
 __global__ __launch_bounds__(TB) void k_loss_final(const float* __restrict__ part, int nb, float scale,
@@ -345,8 +393,14 @@ size_t densify_ws_layout(int64_t n, char* base, DensifyWs* w) {
 bool params_ok(const fh_params* p) {
     return p && p->means && p->log_scales && p->quats && p->logit_opacity && p->sh;
 }
-ParamSet to_set(const fh_params* p) {
-    return ParamSet{p->means, p->log_scales, p->quats, p->logit_opacity, p->sh};
+RowJob row_job(const void* in, void* out, int64_t row_bytes, int zero_new) {
+    const uintptr_t at = reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out) | (uintptr_t)row_bytes;
+    const int ub = at % 16 == 0 ? 16 : (at % 4 == 0 ? 4 : 1);
+    return RowJob{static_cast<const uint8_t*>(in), static_cast<uint8_t*>(out), row_bytes / ub, ub, zero_new};
+}
+void launch_rows(const RowJobs& r, int jobs, hipStream_t s) {
+    const unsigned nb = (unsigned)((r.map.n + ROW_PARENTS - 1) / ROW_PARENTS);
+    if (nb > 0) hipLaunchKernelGGL(k_densify_rows, dim3(nb, jobs), dim3(TB), 0, s, r);
 }
 fh_status status_of_launch() { return hipGetLastError() == hipSuccess ? FH_OK : FH_E_HIP; }
 }  // namespace
@@ -436,24 +490,36 @@ fh_status fh_densify_apply(int64_t n, int32_t sh_degree, const void* dws, const 
         return FH_E_INVALID;
     DensifyWs w;
     densify_ws_layout(n, static_cast<char*>(const_cast<void*>(dws)), &w);
+    const DensifyMap map{n, n_keep, w.action, w.keep_off, w.extra_off, w.keep};
     DensifyApplyArgs a;
-    a.n = n;
-    a.n_keep = n_keep;
-    a.nsh = 3 * (sh_degree + 1) * (sh_degree + 1);
-    a.action = w.action;
-    a.keep = w.keep;
-    a.keep_off = w.keep_off;
-    a.extra_off = w.extra_off;
-    a.in = to_set(in);
-    a.m_in = to_set(m_in);
-    a.v_in = to_set(v_in);
+    a.map = map;
+    a.means = in->means;
+    a.log_scales = in->log_scales;
+    a.quats = in->quats;
+    a.logit = in->logit_opacity;
     a.z = z;
-    a.out = to_set(out);
-    a.m_out = to_set(m_out);
-    a.v_out = to_set(v_out);
+    a.means_out = out->means;
+    a.log_scales_out = out->log_scales;
+    a.logit_out = out->logit_opacity;
     a.scales_out = scales_out;
     a.opacity_out = opacity_out;
     hipLaunchKernelGGL(k_densify_apply, dim3(grid_for(n)), dim3(TB), 0, s, a);
+    const int64_t nsh = 4 * 3 * (int64_t)(sh_degree + 1) * (sh_degree + 1);
+    RowJobs r;
+    r.map = map;
+    int k = 0;
+    r.job[k++] = row_job(in->quats, out->quats, 16, 0);
+    r.job[k++] = row_job(in->sh, out->sh, nsh, 0);
+    const fh_params* mi[2] = {m_in, v_in};
+    const fh_params* mo[2] = {m_out, v_out};
+    for (int c = 0; c < 2; ++c) {
+        r.job[k++] = row_job(mi[c]->means, mo[c]->means, 12, 1);
+        r.job[k++] = row_job(mi[c]->log_scales, mo[c]->log_scales, 12, 1);
+        r.job[k++] = row_job(mi[c]->quats, mo[c]->quats, 16, 1);
+        r.job[k++] = row_job(mi[c]->logit_opacity, mo[c]->logit_opacity, 4, 1);
+        r.job[k++] = row_job(mi[c]->sh, mo[c]->sh, nsh, 1);
+    }
+    launch_rows(r, k, s);
     return status_of_launch();
 }
 
@@ -465,9 +531,10 @@ fh_status fh_densify_copy_rows(int64_t n, const void* dws, const void* in, void*
     if (!in || !out) return FH_E_INVALID;
     DensifyWs w;
     densify_ws_layout(n, static_cast<char*>(const_cast<void*>(dws)), &w);
-    hipLaunchKernelGGL(k_densify_copy_rows, dim3(grid_for(n)), dim3(TB), 0, s, n, n_keep, (const uint32_t*)w.action,
-                       (const uint32_t*)w.keep, (const uint32_t*)w.keep_off, (const uint32_t*)w.extra_off,
-                       static_cast<const uint8_t*>(in), static_cast<uint8_t*>(out), row_bytes);
+    RowJobs r;
+    r.map = DensifyMap{n, n_keep, w.action, w.keep_off, w.extra_off, w.keep};
+    r.job[0] = row_job(in, out, row_bytes, 0);
+    launch_rows(r, 1, s);
     return status_of_launch();
 }
 
@@ -485,7 +552,9 @@ fh_status fh_photometric_loss(int64_t n_pixels, const float* C, const float* C_t
     if (nb > 0x7fffffff) return FH_E_UNSUPPORTED;
     const float scale = (float)(1.0 / (double)count);
     float* part = static_cast<float*>(lws);
-    hipLaunchKernelGGL(k_loss_partial, dim3((unsigned)nb), dim3(TB), 0, s, C, C_target, count, scale, dC, part);
+    const int vec = (reinterpret_cast<uintptr_t>(C) | reinterpret_cast<uintptr_t>(C_target) |
+                     reinterpret_cast<uintptr_t>(dC)) % 16 == 0;
+    hipLaunchKernelGGL(k_loss_partial, dim3((unsigned)nb), dim3(LOSS_TB), 0, s, C, C_target, count, scale, dC, part, vec);
     hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(TB), 0, s, (const float*)part, (int)nb, scale, loss);
     return status_of_launch();
 }
