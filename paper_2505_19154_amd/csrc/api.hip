@@ -603,6 +603,7 @@ static void fill_reduce_args(const fh_plan* p, void* ws, ReduceArgs& r) {
     r.part_geom = cbuf<float>(p, ws, WS_PART_GEOM);
     r.wslot = p->primitive == FH_PRIM_SURFEL ? 13 : 9;
     r.grad2d = buf<float>(p, ws, WS_GRAD2D);
+    r.visited = buf<uint32_t>(p, ws, WS_ORDER_TMP);   // (scratch of the depth sort: free once the order stands)
     r.rank_of = cbuf<uint32_t>(p, ws, WS_RANK_OF);
     r.part_fuse = cbuf<float>(p, ws, WS_PART_FUSE);
     r.d = p->d;
@@ -682,7 +683,10 @@ fh_status fh_render_bwd(const fh_plan* p, const fh_gaussians* g, void* ws, const
     fill_reduce_args(p, ws, r);
     prof_begin(FH_K_REDUCE, s);
     visit_sort(p, ws, s);
-    if (p->n > 0) launch_reduce_geom(r, geom_w(p), s);
+    if (p->n > 0) {
+        launch_fill_u32(r.visited, p->n, 0u, s);
+        launch_reduce_geom(r, geom_w(p), s);
+    }
     if (fuse) {
         r.acc_sum = acc->sum;
         r.acc_comp = acc->comp;
@@ -701,7 +705,7 @@ fh_status fh_render_bwd(const fh_plan* p, const fh_gaussians* g, void* ws, const
     pb.n = (int)p->n;
     pb.sh_degree = p->sh_degree;
     pb.grad2d = r.grad2d;
-    pb.depth_key = cbuf<uint32_t>(p, ws, WS_DEPTH_KEY);
+    pb.visited = r.visited;
     pb.counters = cbuf<Counters>(p, ws, WS_COUNTERS);
     pb.g_means = out->means;
     pb.g_scales = out->scales;
@@ -709,7 +713,7 @@ fh_status fh_render_bwd(const fh_plan* p, const fh_gaussians* g, void* ws, const
     pb.g_opacity = out->opacity;
     pb.g_sh = out->sh;
     prof_begin(FH_K_PROJECT_BWD, s);
-    if (p->n > 0) launch_project_bwd(pb, cam_table(*p), p->n_views, s);
+    if (p->n > 0) launch_project_bwd(pb, cam_table(*p), s);
     prof_end(FH_K_PROJECT_BWD, s);
     return launch_status();
 }

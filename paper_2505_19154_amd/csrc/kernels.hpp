@@ -19,13 +19,13 @@ struct ProjectBwdArgs {
     const float *means, *scales, *quats, *opacity, *sh;
     int n, sh_degree;
     const float* grad2d;
-    const uint32_t* depth_key;
+    const uint32_t* visited;    // [n] bit v: view v visited an instance of the Gaussian (after no overflow)
     const Counters* counters;   // an instance or visit overflow leaves the (zero-filled) outputs zero
     float *g_means, *g_scales, *g_quats, *g_opacity, *g_sh;
     int prim;                   // fh_primitive (surfel adjoint rows: 16 floats)
 };
 void launch_project(const ProjectArgs&, const CamTable&, const ViewTable&, int, hipStream_t);
-void launch_project_bwd(const ProjectBwdArgs&, const CamTable&, int, hipStream_t);
+void launch_project_bwd(const ProjectBwdArgs&, const CamTable&, hipStream_t);
 // sort.hip
 size_t scan_scratch_u32(int64_t n);
 void device_exclusive_scan(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* scratch, int write_total,
@@ -145,6 +145,7 @@ struct ReduceArgs {
     int64_t n, total;
     const float* part_geom;
     float* grad2d;
+    uint32_t* visited;         // [n] zeroed; bit v set for every visited (view v, Gaussian)
     const uint32_t* rank_of;
     const float* part_fuse;
     int d;

@@ -482,31 +482,40 @@ __device__ __forceinline__ void quat_adjoint(const double* qn, double qnorm, con
 }
 
 // colour: rgb = max(0, sum_b sh_b Y_b(dir) + 1/2), dir = (mu - cam) / |mu - cam|;
-// urgb_in: the view's adjoint of rgb
-__device__ __forceinline__ void colour_adjoint(const ProjectBwdArgs& a, const fh_camera& cam, const float* mu,
-                                               const float* shg, int nb, const float* urgb_in, float* gmu,
-                                               float (*gsh)[3]) {
+// urgb_in: the view's adjoint of rgb.  DEG: the SH degree, known at compile time so
+// that the basis, its gradient and the accumulated gsh stay in registers.
+template <int DEG>
+__device__ __forceinline__ void colour_adjoint(const fh_camera& cam, const float* mu, const float* shg,
+                                               const float* urgb_in, float* gmu, float (*gsh)[3]) {
+    constexpr int nb = (DEG + 1) * (DEG + 1);
     // the offset from the camera centre in FP64, rounded once: a component near
     // zero keeps its relative accuracy, and with it the SH gradient Y_b(dir) urgb
     double cpd[3];
+#pragma unroll
     for (int k = 0; k < 3; ++k)
         cpd[k] = -((double)cam.R[k] * cam.t[0] + (double)cam.R[3 + k] * cam.t[1] + (double)cam.R[6 + k] * cam.t[2]);
     const float ddx = (float)(mu[0] - cpd[0]), ddy = (float)(mu[1] - cpd[1]), ddz = (float)(mu[2] - cpd[2]);
     const float il = 1.0f / sqrtf(ddx * ddx + ddy * ddy + ddz * ddz);
     const float dx = ddx * il, dy = ddy * il, dz = ddz * il;
     float Y[16];
-    sh_basis(a.sh_degree, dx, dy, dz, Y);
+    sh_basis(DEG, dx, dy, dz, Y);
     float raw[3] = {0.5f, 0.5f, 0.5f};
+#pragma unroll
     for (int b = 0; b < nb; ++b)
+#pragma unroll
         for (int ch = 0; ch < 3; ++ch) raw[ch] += shg[3 * b + ch] * Y[b];
     float urgb[3];
+#pragma unroll
     for (int ch = 0; ch < 3; ++ch) urgb[ch] = raw[ch] > 0.0f ? urgb_in[ch] : 0.0f;
+#pragma unroll
     for (int b = 0; b < nb; ++b)
+#pragma unroll
         for (int ch = 0; ch < 3; ++ch) gsh[b][ch] += Y[b] * urgb[ch];
-    if (a.sh_degree > 0) {
+    if constexpr (DEG > 0) {
         float GY[16][3];
-        sh_basis_grad(a.sh_degree, dx, dy, dz, GY);
+        sh_basis_grad(DEG, dx, dy, dz, GY);
         float udir[3] = {0, 0, 0};
+#pragma unroll
         for (int b = 1; b < nb; ++b) {
             const float s = shg[3 * b] * urgb[0] + shg[3 * b + 1] * urgb[1] + shg[3 * b + 2] * urgb[2];
             udir[0] += GY[b][0] * s;
@@ -520,8 +529,11 @@ __device__ __forceinline__ void colour_adjoint(const ProjectBwdArgs& a, const fh
     }
 }
 
-__device__ __forceinline__ void store_grads(const ProjectBwdArgs& a, int g, int nb, const float* gmu, const float* gs,
+template <int DEG>
+__device__ __forceinline__ void store_grads(const ProjectBwdArgs& a, int g, const float* gmu, const float* gs,
                                             const float* gq, float gop, const float (*gsh)[3]) {
+    constexpr int nb = (DEG + 1) * (DEG + 1);
+#pragma unroll
     for (int k = 0; k < 3; ++k) {
         a.g_means[3 * g + k] = gmu[k];
         a.g_scales[3 * g + k] = gs[k];
@@ -536,7 +548,9 @@ __device__ __forceinline__ void store_grads(const ProjectBwdArgs& a, int g, int 
 #pragma unroll
         for (int k = 0; k < 12; ++k) o4[k] = make_float4(f[4 * k], f[4 * k + 1], f[4 * k + 2], f[4 * k + 3]);
     } else {
+#pragma unroll
         for (int b = 0; b < nb; ++b)
+#pragma unroll
             for (int ch = 0; ch < 3; ++ch) gsho[3 * b + ch] = gsh[b][ch];
     }
 }
@@ -560,36 +574,38 @@ __device__ __forceinline__ bool upstream_zero(const float* grad2d, size_t j) {
 
 // The outputs are zero-filled before the launch; a Gaussian whose views all
 // pass zero upstream terms (no visited instance reached it) keeps them: every
-// chained term would be zero.
-__global__ __launch_bounds__(256) void k_project_bwd(ProjectBwdArgs a, CamTable ct, int n_views) {
+// chained term would be zero.  visited: bit v of a Gaussian's word says that
+// view v visited an instance of it (set by the geometry reduction), so the
+// others cost four bytes (of 500k Gaussians at 1920x1080 about 2,000 are
+// visited; reading every adjoint row of every view instead took 80 us there and
+// 1.35 ms for 1M Gaussians in 16 views, with the SH arrays in scratch memory).
+template <int DEG>
+__global__ __launch_bounds__(256) void k_project_bwd(ProjectBwdArgs a, CamTable ct) {
     const int g = blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= a.n) return;
     // after an overflow the per-(view, Gaussian) adjoints were not recomputed
     // (they hold an earlier call's values): leave the gradients zero
     if (a.counters->inst_overflow || a.counters->visit_overflow) return;
-    bool any = false;
-    for (int v = 0; v < n_views && !any; ++v) {
-        const size_t j = (size_t)v * a.n + g;
-        any = a.depth_key[j] != CULLED_KEY && !upstream_zero(a.grad2d, j);
-    }
-    if (!any) return;
+    uint32_t views = a.visited[g];
+    if (views == 0u) return;
     const float mu[3] = {a.means[3 * g], a.means[3 * g + 1], a.means[3 * g + 2]};
     const float sc[3] = {a.scales[3 * g], a.scales[3 * g + 1], a.scales[3 * g + 2]};
     const float4 q4 = reinterpret_cast<const float4*>(a.quats)[g];
     const float q[4] = {q4.x, q4.y, q4.z, q4.w};
     const float op = a.opacity[g];
-    const int nb = (a.sh_degree + 1) * (a.sh_degree + 1);
+    constexpr int nb = (DEG + 1) * (DEG + 1);
     const float* shg = a.sh + (size_t)g * nb * 3;
 
     float gmu[3] = {0, 0, 0}, gs[3] = {0, 0, 0}, gq[4] = {0, 0, 0, 0}, gop = 0.0f;
-    float gsh[16][3];
-    for (int b = 0; b < 16; ++b) gsh[b][0] = gsh[b][1] = gsh[b][2] = 0.0f;
+    float gsh[nb][3];
+#pragma unroll
+    for (int b = 0; b < nb; ++b) gsh[b][0] = gsh[b][1] = gsh[b][2] = 0.0f;
 
-    for (int v = 0; v < n_views; ++v) {
+    for (; views != 0u; views &= views - 1u) {   // (views in order)
+        const int v = __builtin_ctz(views);
         const size_t j = (size_t)v * a.n + g;
-        // (a view that no visited instance of this Gaussian reached passes zero
-        // upstream terms: every chained term below is then zero)
-        if (a.depth_key[j] == CULLED_KEY || upstream_zero(a.grad2d, j)) continue;
+        // (zero upstream terms: every chained term below is then zero)
+        if (upstream_zero(a.grad2d, j)) continue;
         const float* g2 = a.grad2d + j * 12;
         const fh_camera& cam = ct.cam[v];
         const Cov64 cv = cov64(mu, sc, q, cam);
@@ -647,38 +663,37 @@ __global__ __launch_bounds__(256) void k_project_bwd(ProjectBwdArgs a, CamTable 
             gs[l] += upM[0][l] * (float)cv.Rq[0][l] + upM[1][l] * (float)cv.Rq[1][l] + upM[2][l] * (float)cv.Rq[2][l];
 
         quat_adjoint(cv.qn, cv.qnorm, upR, gq);
-        colour_adjoint(a, cam, mu, shg, nb, g2 + 6, gmu, gsh);
+        colour_adjoint<DEG>(cam, mu, shg, g2 + 6, gmu, gsh);
     }
-    store_grads(a, g, nb, gmu, gs, gq, gop, gsh);
+    store_grads<DEG>(a, g, gmu, gs, gq, gop, gsh);
 }
 
 // Surfel adjoint, views in view order.  grad2d[(v*N + g)*16 + k], k: 0..8
 // the record entries (x_c, y_c, a0, a1, b0, b1, D, e1, e2), 9 sum dL/dpower,
 // 10..12 rgb, 13 sum w.  The chain in FP64: (D, e1, e2) -> (a, b, c), then
 // (x_c, y_c, a, b, c) -> (p, T_u, T_v) -> (mu, s_u, s_v, q).
-__global__ __launch_bounds__(256) void k_project_bwd_surfel(ProjectBwdArgs a, CamTable ct, int n_views) {
+template <int DEG>
+__global__ __launch_bounds__(256) void k_project_bwd_surfel(ProjectBwdArgs a, CamTable ct) {
     const int g = blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= a.n) return;
     if (a.counters->inst_overflow || a.counters->visit_overflow) return;
-    bool any = false;
-    for (int v = 0; v < n_views && !any; ++v) {
-        const size_t j = (size_t)v * a.n + g;
-        any = a.depth_key[j] != CULLED_KEY && !upstream_zero<16>(a.grad2d, j);
-    }
-    if (!any) return;
+    uint32_t views = a.visited[g];
+    if (views == 0u) return;
     const float mu[3] = {a.means[3 * g], a.means[3 * g + 1], a.means[3 * g + 2]};
     const float sc[3] = {a.scales[3 * g], a.scales[3 * g + 1], a.scales[3 * g + 2]};
     const float4 q4 = reinterpret_cast<const float4*>(a.quats)[g];
     const float q[4] = {q4.x, q4.y, q4.z, q4.w};
     const float op = a.opacity[g];
-    const int nb = (a.sh_degree + 1) * (a.sh_degree + 1);
+    constexpr int nb = (DEG + 1) * (DEG + 1);
     const float* shg = a.sh + (size_t)g * nb * 3;
     float gmu[3] = {0, 0, 0}, gs[3] = {0, 0, 0}, gq[4] = {0, 0, 0, 0}, gop = 0.0f;
-    float gsh[16][3];
-    for (int b = 0; b < 16; ++b) gsh[b][0] = gsh[b][1] = gsh[b][2] = 0.0f;
-    for (int v = 0; v < n_views; ++v) {
+    float gsh[nb][3];
+#pragma unroll
+    for (int b = 0; b < nb; ++b) gsh[b][0] = gsh[b][1] = gsh[b][2] = 0.0f;
+    for (; views != 0u; views &= views - 1u) {
+        const int v = __builtin_ctz(views);
         const size_t j = (size_t)v * a.n + g;
-        if (a.depth_key[j] == CULLED_KEY || upstream_zero<16>(a.grad2d, j)) continue;
+        if (upstream_zero<16>(a.grad2d, j)) continue;
         const float* g2 = a.grad2d + j * 16;
         const fh_camera& cam = ct.cam[v];
         const Srf64 f = srf64(mu, sc, q, cam);
@@ -722,9 +737,9 @@ __global__ __launch_bounds__(256) void k_project_bwd_surfel(ProjectBwdArgs a, Ca
             upR[k][2] = 0.0f;
         }
         quat_adjoint(f.qn, f.qnorm, upR, gq);
-        colour_adjoint(a, cam, mu, shg, nb, g2 + 10, gmu, gsh);
+        colour_adjoint<DEG>(cam, mu, shg, g2 + 10, gmu, gsh);
     }
-    store_grads(a, g, nb, gmu, gs, gq, gop, gsh);
+    store_grads<DEG>(a, g, gmu, gs, gq, gop, gsh);
 }
 
 // ---------------------------------------------------------------------------
@@ -736,17 +751,43 @@ void launch_project(const ProjectArgs& a, const CamTable& ct, const ViewTable& v
         hipLaunchKernelGGL(k_project, grid, dim3(256), 0, s, a, ct, vt);
 }
 
-void launch_project_bwd(const ProjectBwdArgs& a, const CamTable& ct, int n_views, hipStream_t s) {
-    const int64_t nsh = (int64_t)(a.sh_degree + 1) * (a.sh_degree + 1) * 3;
-    launch_fill_u32(reinterpret_cast<uint32_t*>(a.g_means), (int64_t)a.n * 3, 0u, s);
-    launch_fill_u32(reinterpret_cast<uint32_t*>(a.g_scales), (int64_t)a.n * 3, 0u, s);
-    launch_fill_u32(reinterpret_cast<uint32_t*>(a.g_quats), (int64_t)a.n * 4, 0u, s);
-    launch_fill_u32(reinterpret_cast<uint32_t*>(a.g_opacity), (int64_t)a.n, 0u, s);
-    launch_fill_u32(reinterpret_cast<uint32_t*>(a.g_sh), (int64_t)a.n * nsh, 0u, s);
+// Zero the five gradient arrays in one launch: 16 bytes a thread where an array
+// is aligned to them, the rest element by element.
+struct ZeroArgs {
+    float* p[5];
+    int64_t n[5];
+};
+__global__ __launch_bounds__(256) void k_zero_grads(ZeroArgs a) {
+    const int64_t i0 = (int64_t)blockIdx.x * 256 + threadIdx.x, stride = (int64_t)gridDim.x * 256;
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        const int64_t n4 = reinterpret_cast<uintptr_t>(a.p[k]) % 16 == 0 ? a.n[k] / 4 : 0;
+        for (int64_t i = i0; i < n4; i += stride) reinterpret_cast<float4*>(a.p[k])[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int64_t i = 4 * n4 + i0; i < a.n[k]; i += stride) a.p[k][i] = 0.0f;
+    }
+}
+
+template <int DEG>
+static void launch_project_bwd_deg(const ProjectBwdArgs& a, const CamTable& ct, hipStream_t s) {
+    const dim3 grid((a.n + 255) / 256);
     if (a.prim == FH_PRIM_SURFEL)
-        hipLaunchKernelGGL(k_project_bwd_surfel, dim3((a.n + 255) / 256), dim3(256), 0, s, a, ct, n_views);
+        hipLaunchKernelGGL(k_project_bwd_surfel<DEG>, grid, dim3(256), 0, s, a, ct);
     else
-        hipLaunchKernelGGL(k_project_bwd, dim3((a.n + 255) / 256), dim3(256), 0, s, a, ct, n_views);
+        hipLaunchKernelGGL(k_project_bwd<DEG>, grid, dim3(256), 0, s, a, ct);
+}
+
+void launch_project_bwd(const ProjectBwdArgs& a, const CamTable& ct, hipStream_t s) {
+    const int64_t nsh = (int64_t)(a.sh_degree + 1) * (a.sh_degree + 1) * 3;
+    const ZeroArgs z{{a.g_means, a.g_scales, a.g_quats, a.g_opacity, a.g_sh},
+                     {(int64_t)a.n * 3, (int64_t)a.n * 3, (int64_t)a.n * 4, (int64_t)a.n, (int64_t)a.n * nsh}};
+    const int64_t nb = ((int64_t)a.n * nsh / 4 + 255) / 256;
+    hipLaunchKernelGGL(k_zero_grads, dim3((unsigned)(nb < 1 ? 1 : (nb > 8192 ? 8192 : nb))), dim3(256), 0, s, z);
+    switch (a.sh_degree) {
+        case 0: launch_project_bwd_deg<0>(a, ct, s); break;
+        case 1: launch_project_bwd_deg<1>(a, ct, s); break;
+        case 2: launch_project_bwd_deg<2>(a, ct, s); break;
+        default: launch_project_bwd_deg<3>(a, ct, s); break;
+    }
 }
 
 }  // namespace fh

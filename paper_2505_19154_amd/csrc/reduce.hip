@@ -156,12 +156,13 @@ __global__ __launch_bounds__(256) void k_reduce_geom(ReduceArgs a) {
     const bool is_long = b1 - b0 > LONG_GEOM;
     const uint32_t slot = wave_slot(&a.counters->n_long_geom, is_long);
     if (!valid) return;
+    const int64_t v = j / a.n;
+    const uint32_t g = a.order[j];
+    if (b1 > b0) atomicOr(&a.visited[g], 1u << v);
     if (is_long) {
         a.long_list[slot] = (uint32_t)j;
         return;
     }
-    const int64_t v = j / a.n;
-    const uint32_t g = a.order[j];
     float acc[GP];
 #pragma unroll
     for (int m = 0; m < GP; ++m) acc[m] = 0.0f;

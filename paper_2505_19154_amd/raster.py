@@ -180,6 +180,7 @@ class Rasterizer:
         if self.ndfd:
             L.check(self.lib.fh_plan_set_ndfd(ctypes.byref(plan), 1), "fh_plan_set_ndfd")
         self.plan = plan
+        self.ws = None                # the old workspace is given back before the new one is taken
         self.ws = torch.empty(max(int(plan.ws_bytes), 256), dtype=torch.uint8, device=self.device)
         self.generation += 1
 
@@ -468,8 +469,9 @@ class Rasterizer:
     def forward(self, g: Gaussians, margin: float = 1.05) -> Image:
         """prepare + render_fwd, growing the visit capacity until it fits."""
         self.prepare(g, margin)
+        img = None
         while True:
-            img = self.render_fwd(g)
+            img = self.render_fwd(g, img)
             c = self.counters()
             if not c.visit_overflow and self.plan.visit_capacity > 0:
                 return img
