@@ -299,11 +299,9 @@ static void plan_layout(fh_plan* plan) {
     sz[WS_PART_NDFD] = plan->ndfd ? (size_t)visit_capacity * 2 * ndfd_part_floats(plan->primitive) * sizeof(float) : 0;
     sz[WS_NDFD_SC] = plan->ndfd ? (size_t)visit_capacity * TILE_PIX * 2 * sizeof(float) : 0;
     sz[WS_TORDER_KA] = sz[WS_TORDER_KB] = sz[WS_TORDER_VA] = sz[WS_TORDER_VB] = (size_t)tiles * u4;
-    // the BF16 gradient kernel records w for the fusion kernel of the same call
-    sz[WS_WREC] = (plan->form == FH_FORM_BF16 && d > 0 && render_bwd_bf16_supported(d))
-                      ? (size_t)visit_capacity * TILE_PIX * sizeof(float) : 0;
-    sz[WS_GREC] = (plan->form == FH_FORM_BF16 && d > 0 && render_bwd_bf16_sliced(d))
-                      ? (size_t)visit_capacity * TILE_PIX * sizeof(float) : 0;
+    // f . dF per visited (position, pixel) (see launch_bwd)
+    sz[WS_WREC] = (plan->form == FH_FORM_BF16 && d == 256) ? (size_t)visit_capacity * TILE_PIX * sizeof(float) : 0;
+    sz[WS_GREC] = (plan->form == FH_FORM_BF16 && d > 256) ? (size_t)visit_capacity * TILE_PIX * sizeof(float) : 0;
     static_assert(WS_COUNT <= FH_WS_SLOTS, "fh_plan.off holds the offset of every workspace sub-buffer");
     size_t off = 0;
     plan->n_ws = WS_COUNT;
@@ -529,28 +527,26 @@ static void fill_bwd_args(const fh_plan* p, const fh_gaussians* g, void* ws, con
     a.part_geom = buf<float>(p, ws, WS_PART_GEOM);
     a.part_fuse = buf<float>(p, ws, WS_PART_FUSE);
     a.tile_order = nullptr;
-    a.wrec = nullptr;
+    a.g = nullptr;
     a.d0 = 0;
-    a.g_in = nullptr;
-    a.g_out = nullptr;
     a.prim = p->primitive;
 }
 
 static int visit_sort_passes(const fh_plan* p) { return (p->rank_bits + 7) / 8; }
 
-// The form's adjoint and fusion kernels.
+// The adjoint and fusion kernels.  f . dF of widths from 256 channels up goes
+// through memory ([visits][256] floats): the BF16 form's plans hold it
+// (WS_GREC above 256 channels, WS_WREC at 256); the FP32 form lends the fusion
+// partials, which have at least 256 floats a visit then and are written after
+// the walk has read it.
 static void launch_bwd(const fh_plan* p, void* ws, const BwdArgs& a0, const ViewTable& vt, bool fuse, hipStream_t s) {
-    if (p->form == FH_FORM_BF16 && render_bwd_bf16_supported(p->d)) {
-        BwdArgs a = a0;
-        a.tile_order = tile_schedule(p, ws, false, s);
-        // the gradient kernel records w when the fusion kernel follows it
-        a.wrec = (fuse && a.dC != nullptr) ? buf<float>(p, ws, WS_WREC) : nullptr;
-        if (render_bwd_bf16_sliced(p->d)) a.g_out = buf<float>(p, ws, WS_GREC);
-        launch_render_bwd_bf16(a, vt, (int)p->n_tiles, a.dC != nullptr, fuse, s);
-    } else {
-        const BwdArgs& a = a0;
-        launch_render_bwd_f32(a, vt, (int)p->n_tiles, a.dC != nullptr, fuse, s);
-    }
+    BwdArgs a = a0;
+    const bool bf16 = p->form == FH_FORM_BF16;
+    if (bf16) a.tile_order = tile_schedule(p, ws, false, s);
+    if (p->d >= 256)
+        a.g = bf16 ? buf<float>(p, ws, p->d > 256 ? WS_GREC : WS_WREC) : buf<float>(p, ws, WS_PART_FUSE);
+    if (a.dC != nullptr) launch_render_grad(a, vt, (int)p->n_tiles, bf16, s);
+    if (fuse) launch_render_fuse(a, vt, (int)p->n_tiles, bf16, a.dC == nullptr, s);
 }
 
 // Rank, Gaussian and record of every visited instance, in visit order.
@@ -807,7 +803,7 @@ fh_status fh_tuning_candidates(const fh_plan* p, int32_t which, fh_tuning* out, 
                 out[n] = p->tuning;
                 out[n++].bwd_chunk = ch;
             }
-    } else if (which == FH_K_RENDER_BWD && p->form == FH_FORM_BF16 && render_bwd_bf16_supported(p->d)) {
+    } else if (which == FH_K_RENDER_BWD && p->form == FH_FORM_BF16) {
         for (int sc : {0, 1})
             if (n < max) {
                 out[n] = p->tuning;

@@ -66,8 +66,8 @@ enum WsBuf {
     WS_TORDER_KB,
     WS_TORDER_VA,      // u32 [tiles] tile schedule: tile ids (ping-pong; the order ends here)
     WS_TORDER_VB,
-    WS_WREC,           // float [visit_cap * 256] w per visited (position, pixel), BF16 form (gradient -> fusion)
-    WS_GREC,           // float [visit_cap * 256] f . dF of earlier channel slices, BF16 form above 256 channels
+    WS_WREC,           // float [visit_cap * 256] f . dF per visited (position, pixel), BF16 form at 256 channels
+    WS_GREC,           // the same above 256 channels
     WS_COUNT
 };
 

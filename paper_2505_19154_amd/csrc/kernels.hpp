@@ -106,16 +106,12 @@ struct BwdArgs {
     float* part_geom;
     float* part_fuse;
     const uint32_t* tile_order;   // nullable: work item i takes tile tile_order[i]
-    float* wrec;                  // nullable: [visits][256] w of every visited (position, pixel), recorded by the
-                                  // BF16 gradient kernel for the fusion kernel of the same call
-    // BF16 kernels at feature widths above 256 work in channel slices: the
-    // slice starts at channel d0 (rows of feat, dF, target and the fusion
-    // partials keep the stride d); g = f . dF of the earlier slices is carried
-    // between launches in [visits][256] rows (g_in added, g_out written)
+    // widths of 256 channels and up: [visits][256] f . dF of every visited
+    // (position, pixel), written by the contraction kernel a slice at a time
+    // (from channel d0) and read by the walk
+    float* g;
     int d0;
-    const float* g_in;
-    float* g_out;
-    int prim;                     // fh_primitive (FP32 VALU kernels)
+    int prim;                     // fh_primitive
 };
 struct VisitStageArgs {
     const uint32_t* ranges;
@@ -158,15 +154,15 @@ void launch_render_fwd_f32(const RenderArgs& a, const ViewTable& vt, int n_tiles
 bool render_fwd_bf16_shape_ok(int d, int slice, int rows);
 void launch_render_fwd_bf16(const RenderArgs& a, const ViewTable& vt, int n_tiles, int slice, int rows, bool fsplit,
                             hipStream_t s);
-bool render_bwd_bf16_supported(int d);
-bool render_bwd_bf16_sliced(int d);   // above 256 channels: sliced, with a carry of f . dF between slices
-void launch_render_bwd_bf16(const BwdArgs& a, const ViewTable& vt, int n_tiles, bool grads, bool fuse,
-                            hipStream_t s);
+// render_bwd.hip: the gradient kernel (needs dC); bf16: the BF16 form.  With dF
+// and d >= 256 it needs a.g
+void launch_render_grad(const BwdArgs& a, const ViewTable& vt, int n_tiles, bool bf16, hipStream_t s);
+// render_fuse.hip: the fusion partials (needs the target); ws: also the weight
+// sums, which the gradient kernel of the same call writes otherwise
+void launch_render_fuse(const BwdArgs& a, const ViewTable& vt, int n_tiles, bool bf16, bool ws, hipStream_t s);
 void launch_visit_stage(const VisitStageArgs& a, int n_tiles, hipStream_t s);
 void launch_vseg(const uint32_t* skeys, const Counters* c, int64_t cap, uint32_t* vseg, hipStream_t s);
 void launch_check_visits(const uint32_t* tile_voff, int n_tiles, Counters* c, int64_t cap, hipStream_t s);
-// render_bwd_f32.hip.  grads: the gradient kernel (needs dC); fuse: the fusion kernel (needs the target)
-void launch_render_bwd_f32(const BwdArgs& a, const ViewTable& vt, int n_tiles, bool grads, bool fuse, hipStream_t s);
 // gp: floats per partial row, 12 (Gaussians: 10 used) or 16 (surfels: 14 used)
 void launch_reduce_geom(const ReduceArgs& a, int gp, hipStream_t s);
 void launch_reduce_fuse(const ReduceArgs& a, hipStream_t s);
