@@ -207,7 +207,7 @@ __global__ __launch_bounds__(TB) void k_densify_apply(DensifyApplyArgs a) {
 // Rows of per-Gaussian arrays carried to the densified set.  A job is one
 // array: rows of `units` elements (16, 4 or 1 bytes each, as its row size and
 // addresses allow); zero_new: an Adam moment, kept by an original that was not
-// split and zero for every other copy.  A workgroup takes 64 parents and its
+// split and zero for every other copy.  A workgroup takes 32 parents and its
 // threads run over (parent, element), so that neighbouring threads move
 // neighbouring elements of a row (370 us for 1.3 GB at 500k Gaussians with 512-byte
 // features, 3.5 TB/s; one thread per parent, which stepped through
@@ -224,7 +224,8 @@ struct RowJobs {
     RowJob job[MAX_ROW_JOBS];
     DensifyMap map;
 };
-constexpr int ROW_PARENTS = 64;
+constexpr int ROW_PARENTS = 32;
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 template <typename T>
 __device__ __forceinline__ void densify_rows(const RowJob& J, const uint32_t* d0, const uint32_t* d1, const uint8_t* how,
@@ -246,13 +247,24 @@ __device__ __forceinline__ void densify_rows(const RowJob& J, const uint32_t* d0
         return;
     }
     const uint32_t U = (uint32_t)J.units, total = (uint32_t)parents * U;
-    for (uint32_t idx = threadIdx.x; idx < total; idx += TB) {
-        const uint32_t k = idx / U, i = idx - k * U;
-        const uint8_t h = how[k];
-        if (!(h & 1)) continue;                       // pruned
-        const T val = in[idx];
-        out[(int64_t)d0[k] * U + i] = (J.zero_new && (h & 4)) ? zero : val;
-        if (h & 2) out[(n_keep + (int64_t)d1[k]) * U + i] = J.zero_new ? zero : val;
+    // four elements a thread requested before any is stored
+    for (uint32_t i0 = threadIdx.x; i0 < total; i0 += 4 * TB) {
+        T val[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t idx = i0 + e * TB;
+            val[e] = idx < total ? in[idx] : zero;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t idx = i0 + e * TB;
+            if (idx >= total) break;
+            const uint32_t k = idx / U, i = idx - k * U;
+            const uint8_t h = how[k];
+            if (!(h & 1)) continue;                   // pruned
+            out[(int64_t)d0[k] * U + i] = (J.zero_new && (h & 4)) ? zero : val[e];
+            if (h & 2) out[(n_keep + (int64_t)d1[k]) * U + i] = J.zero_new ? zero : val[e];
+        }
     }
 }
 
@@ -269,9 +281,23 @@ __global__ __launch_bounds__(TB) void k_densify_rows(RowJobs a) {
         how[threadIdx.x] = a.map.keep[g] ? (uint8_t)(1u | (act != 0u ? 2u : 0u) | (act == 2u ? 4u : 0u)) : 0;
     }
     __syncthreads();
-    const RowJob& J = a.job[blockIdx.y];
+    // (selected with constant indices, field by field: the argument stays out of scratch memory)
+    const uint8_t* in = a.job[0].in;
+    uint8_t* out = a.job[0].out;
+    int64_t units = a.job[0].units;
+    int unit_bytes = a.job[0].unit_bytes, zero_new = a.job[0].zero_new;
+#pragma unroll
+    for (int k = 1; k < MAX_ROW_JOBS; ++k) {
+        const bool me = (int)blockIdx.y == k;
+        in = me ? a.job[k].in : in;
+        out = me ? a.job[k].out : out;
+        units = me ? a.job[k].units : units;
+        unit_bytes = me ? a.job[k].unit_bytes : unit_bytes;
+        zero_new = me ? a.job[k].zero_new : zero_new;
+    }
+    const RowJob J{in, out, units, unit_bytes, zero_new};
     if (J.unit_bytes == 16)
-        densify_rows<uint4>(J, d0, d1, how, g0, parents, a.map.n_keep);
+        densify_rows<u32x4>(J, d0, d1, how, g0, parents, a.map.n_keep);
     else if (J.unit_bytes == 4)
         densify_rows<uint32_t>(J, d0, d1, how, g0, parents, a.map.n_keep);
     else
