@@ -189,27 +189,40 @@ static const uint32_t* tile_schedule(const fh_plan* p, void* ws, bool by_range, 
                           by_range ? nullptr : cbuf<uint32_t>(p, ws, WS_TILE_NITER), p->n_tiles, ka, s);
     const int passes = radix_sort(ka, nullptr, ka, buf<uint32_t>(p, ws, WS_TORDER_VA), buf<uint32_t>(p, ws, WS_TORDER_KB),
                                   buf<uint32_t>(p, ws, WS_TORDER_VB), true, 1, p->n_tiles, nullptr, 0, 0, 16,
-                                  buf<uint32_t>(p, ws, WS_HIST), buf<uint32_t>(p, ws, WS_SCAN_TMP), s);
+                                  buf<uint32_t>(p, ws, WS_HIST), nullptr, s);
     return cbuf<uint32_t>(p, ws, (passes % 2) ? WS_TORDER_VB : WS_TORDER_VA);
 }
 
-// depth sort, tiles per rank, their scan, the instance count and the overflow flag
-static void bin_count_impl(const fh_plan* p, void* ws, hipStream_t s) {
+// depth sort, tiles per rank, their scan, the instance count and the overflow
+// flag; ranges (nullable): the tiles' list ranges, cleared
+static void bin_count_impl(const fh_plan* p, void* ws, uint32_t* ranges, hipStream_t s) {
     const int64_t total = (int64_t)p->n_views * p->n;
     Counters* c = buf<Counters>(p, ws, WS_COUNTERS);
-    hipLaunchKernelGGL(k_reset_bin_counters, dim3(1), dim3(64), 0, s, c);
-    if (total == 0) return;
+    if (total == 0) {
+        hipLaunchKernelGGL(k_reset_bin_counters, dim3(1), dim3(64), 0, s, c);
+        if (ranges) launch_fill_u32(ranges, p->n_tiles * 2, 0u, s);
+        return;
+    }
     uint32_t* hist = buf<uint32_t>(p, ws, WS_HIST);
-    uint32_t* scan_tmp = buf<uint32_t>(p, ws, WS_SCAN_TMP);
     radix_sort(cbuf<uint32_t>(p, ws, WS_DEPTH_KEY), nullptr, buf<uint32_t>(p, ws, WS_DKEY_TMP2),
                buf<uint32_t>(p, ws, WS_ORDER), buf<uint32_t>(p, ws, WS_DKEY_TMP), buf<uint32_t>(p, ws, WS_ORDER_TMP),
-               true, p->n_views, p->n, nullptr, 0, 0, 32, hist, scan_tmp, s);
-    uint32_t* ntiles = buf<uint32_t>(p, ws, WS_DKEY_TMP);
-    launch_tiles_by_rank(cbuf<uint32_t>(p, ws, WS_ORDER), cbuf<int4>(p, ws, WS_RECT), p->n, total, ntiles, c, s);
-    device_exclusive_scan(ntiles, buf<uint32_t>(p, ws, WS_INST_OFF), total, scan_tmp, 1, s);
-    launch_check_capacity(c, p->inst_capacity, s);
-    launch_rank_tables(cbuf<uint32_t>(p, ws, WS_ORDER), cbuf<float4>(p, ws, WS_REC), p->n, total,
-                       buf<uint32_t>(p, ws, WS_RANK_OF), buf<float4>(p, ws, WS_RREC), rec_w(p), s);
+               true, p->n_views, p->n, nullptr, 0, 0, 32, hist, c, s);
+    RankArgs a;
+    a.order = cbuf<uint32_t>(p, ws, WS_ORDER);
+    a.rect = cbuf<int4>(p, ws, WS_RECT);
+    a.rec = cbuf<float4>(p, ws, WS_REC);
+    a.n = p->n;
+    a.total = total;
+    a.cap = p->inst_capacity;
+    a.ntiles = buf<uint32_t>(p, ws, WS_DKEY_TMP);
+    a.inst_off = buf<uint32_t>(p, ws, WS_INST_OFF);
+    a.rank_of = buf<uint32_t>(p, ws, WS_RANK_OF);
+    a.rrec = buf<float4>(p, ws, WS_RREC);
+    a.rw = rec_w(p);
+    a.counters = c;
+    a.ranges = ranges;
+    a.n_ranges = p->n_tiles * 2;
+    launch_ranks(a, hist, buf<uint32_t>(p, ws, WS_SCAN_TMP), s);
 }
 
 // ---------------------------------------------------------------------------
@@ -404,7 +417,7 @@ fh_status fh_project(const fh_plan* p, const fh_gaussians* g, void* ws, hipStrea
 
 fh_status fh_bin_count(const fh_plan* p, void* ws, hipStream_t s) {
     if (!p || !ws) return FH_E_INVALID;
-    bin_count_impl(p, ws, s);
+    bin_count_impl(p, ws, nullptr, s);
     return launch_status();
 }
 
@@ -412,17 +425,17 @@ fh_status fh_bin_sort(const fh_plan* p, void* ws, hipStream_t s) {
     if (!p || !ws) return FH_E_INVALID;
     if (p->inst_capacity <= 0) return FH_E_INVALID;
     prof_begin(FH_K_BIN, s);
-    bin_count_impl(p, ws, s);
+    uint32_t* ranges = buf<uint32_t>(p, ws, WS_RANGES);
+    bin_count_impl(p, ws, ranges, s);
     const int64_t total = (int64_t)p->n_views * p->n;
     const Counters* c = cbuf<Counters>(p, ws, WS_COUNTERS);
-    uint32_t* ranges = buf<uint32_t>(p, ws, WS_RANGES);
-    launch_fill_u32(ranges, p->n_tiles * 2, 0u, s);
     if (total == 0) {
         prof_end(FH_K_BIN, s);
         return launch_status();
     }
     DupArgs da;
     da.inst_off = cbuf<uint32_t>(p, ws, WS_INST_OFF);
+    da.starts = dup_starts(cbuf<uint32_t>(p, ws, WS_HIST), total);
     da.order = cbuf<uint32_t>(p, ws, WS_ORDER);
     da.rect = cbuf<int4>(p, ws, WS_RECT);
     da.n = p->n;
@@ -440,7 +453,7 @@ fh_status fh_bin_sort(const fh_plan* p, void* ws, hipStream_t s) {
                buf<uint32_t>(p, ws, WS_KEYS_A), p->packed_keys ? nullptr : buf<uint32_t>(p, ws, WS_VALS_A),
                buf<uint32_t>(p, ws, WS_KEYS_B), p->packed_keys ? nullptr : buf<uint32_t>(p, ws, WS_VALS_B),
                !p->packed_keys, 1, 0, &c->n_instances, p->inst_capacity, lo, lo + p->tile_bits,
-               buf<uint32_t>(p, ws, WS_HIST), buf<uint32_t>(p, ws, WS_SCAN_TMP), s);
+               buf<uint32_t>(p, ws, WS_HIST), nullptr, s);
     launch_ranges(cbuf<uint32_t>(p, ws, final_keys_buf(p)), c, p->inst_capacity, p->rank_bits, p->packed_keys, ranges,
                   s);
     prof_end(FH_K_BIN, s);
@@ -495,8 +508,8 @@ fh_status fh_render_fwd(const fh_plan* p, const fh_gaussians* g, void* ws, const
         launch_render_fwd_f32(a, vt, (int)p->n_tiles, s);
     prof_end(FH_K_RENDER_FWD, s);
     uint32_t* voff = buf<uint32_t>(p, ws, WS_TILE_VOFF);
-    device_exclusive_scan(tile_niter, voff, p->n_tiles, buf<uint32_t>(p, ws, WS_SCAN_TMP), 1, s);
-    launch_check_visits(voff, (int)p->n_tiles, buf<Counters>(p, ws, WS_COUNTERS), p->visit_capacity, s);
+    launch_scan_visits(tile_niter, voff, p->n_tiles, buf<uint32_t>(p, ws, WS_SCAN_TMP), buf<Counters>(p, ws, WS_COUNTERS),
+                       p->visit_capacity, s);
     return launch_status();
 }
 
@@ -549,8 +562,12 @@ static void launch_bwd(const fh_plan* p, void* ws, const BwdArgs& a0, const View
     if (fuse) launch_render_fuse(a, vt, (int)p->n_tiles, bf16, a.dC == nullptr, s);
 }
 
-// Rank, Gaussian and record of every visited instance, in visit order.
-static void visit_stage(const fh_plan* p, void* ws, hipStream_t s) {
+// Rank, Gaussian and record of every visited instance, in visit order.  For
+// calls that sort them by rank next (VISITS_SORT) the launch also clears the
+// segments and the view bits, of which the words of the depth sort's scratch
+// are the store (free once the order stands).
+enum { VISITS_LIST = 0, VISITS_SORT = 1 };
+static void visit_stage(const fh_plan* p, void* ws, int want, hipStream_t s) {
     VisitStageArgs a;
     a.ranges = cbuf<uint32_t>(p, ws, WS_RANGES);
     a.tile_niter = cbuf<uint32_t>(p, ws, WS_TILE_NITER);
@@ -566,6 +583,10 @@ static void visit_stage(const fh_plan* p, void* ws, hipStream_t s) {
     a.vgid = buf<uint32_t>(p, ws, WS_VGID);
     a.vrec = buf<float4>(p, ws, WS_VREC);
     a.rw = rec_w(p);
+    a.vseg = want == VISITS_SORT ? buf<uint32_t>(p, ws, WS_VSEG) : nullptr;
+    a.n_vseg = (int64_t)p->n * p->n_views * 2;
+    a.visited = want == VISITS_SORT ? buf<uint32_t>(p, ws, WS_ORDER_TMP) : nullptr;
+    a.n = p->n;
     launch_visit_stage(a, (int)p->n_tiles, s);
 }
 
@@ -574,15 +595,13 @@ static void visit_stage(const fh_plan* p, void* ws, hipStream_t s) {
 // tile order.
 static void visit_sort(const fh_plan* p, void* ws, hipStream_t s) {
     Counters* c = buf<Counters>(p, ws, WS_COUNTERS);
-    const int64_t total = (int64_t)p->n * p->n_views;
     uint32_t* vka = buf<uint32_t>(p, ws, WS_VKEY_A);
     radix_sort(vka, nullptr, vka, buf<uint32_t>(p, ws, WS_VVAL_A), buf<uint32_t>(p, ws, WS_VKEY_B),
                buf<uint32_t>(p, ws, WS_VVAL_B), true, 1, 0, &c->n_visited, p->visit_capacity, 0, p->rank_bits,
-               buf<uint32_t>(p, ws, WS_HIST), buf<uint32_t>(p, ws, WS_SCAN_TMP), s);
+               buf<uint32_t>(p, ws, WS_HIST), nullptr, s);
     const bool odd = visit_sort_passes(p) % 2;
-    uint32_t* vseg = buf<uint32_t>(p, ws, WS_VSEG);
-    launch_fill_u32(vseg, total * 2, 0u, s);
-    launch_vseg(cbuf<uint32_t>(p, ws, odd ? WS_VKEY_B : WS_VKEY_A), c, p->visit_capacity, vseg, s);
+    launch_vseg(cbuf<uint32_t>(p, ws, odd ? WS_VKEY_B : WS_VKEY_A), c, p->visit_capacity, buf<uint32_t>(p, ws, WS_VSEG),
+                cbuf<uint32_t>(p, ws, WS_ORDER), p->n, buf<uint32_t>(p, ws, WS_ORDER_TMP), s);
 }
 
 static void fill_reduce_args(const fh_plan* p, void* ws, ReduceArgs& r) {
@@ -599,7 +618,7 @@ static void fill_reduce_args(const fh_plan* p, void* ws, ReduceArgs& r) {
     r.part_geom = cbuf<float>(p, ws, WS_PART_GEOM);
     r.wslot = p->primitive == FH_PRIM_SURFEL ? 13 : 9;
     r.grad2d = buf<float>(p, ws, WS_GRAD2D);
-    r.visited = buf<uint32_t>(p, ws, WS_ORDER_TMP);   // (scratch of the depth sort: free once the order stands)
+    r.visited = cbuf<uint32_t>(p, ws, WS_ORDER_TMP);
     r.rank_of = cbuf<uint32_t>(p, ws, WS_RANK_OF);
     r.part_fuse = cbuf<float>(p, ws, WS_PART_FUSE);
     r.d = p->d;
@@ -658,7 +677,7 @@ fh_status fh_render_bwd(const fh_plan* p, const fh_gaussians* g, void* ws, const
     a.target_bf16 = target_dtype == FH_BF16;
     const ViewTable vt = view_table(*p);
     prof_begin(FH_K_RENDER_BWD, s);
-    visit_stage(p, ws, s);
+    visit_stage(p, ws, VISITS_SORT, s);
     launch_bwd(p, ws, a, vt, fuse, s);
     prof_end(FH_K_RENDER_BWD, s);
     if (ndfd) {
@@ -679,10 +698,7 @@ fh_status fh_render_bwd(const fh_plan* p, const fh_gaussians* g, void* ws, const
     fill_reduce_args(p, ws, r);
     prof_begin(FH_K_REDUCE, s);
     visit_sort(p, ws, s);
-    if (p->n > 0) {
-        launch_fill_u32(r.visited, p->n, 0u, s);
-        launch_reduce_geom(r, geom_w(p), s);
-    }
+    if (p->n > 0) launch_reduce_geom(r, geom_w(p), s);
     if (fuse) {
         r.acc_sum = acc->sum;
         r.acc_comp = acc->comp;
@@ -726,7 +742,7 @@ fh_status fh_ndfd_losses(const fh_plan* p, const fh_gaussians* g, void* ws, cons
     n.Lgt = Lgt;
     n.Lcf = Lcf;
     const ViewTable vt = view_table(*p);
-    visit_stage(p, ws, s);
+    visit_stage(p, ws, VISITS_LIST, s);
     prof_begin(FH_K_NDFD, s);
     launch_ndfd(n, vt, (int)p->n_tiles, false, s);
     prof_end(FH_K_NDFD, s);
@@ -747,7 +763,7 @@ fh_status fh_fuse_features(const fh_plan* p, const fh_gaussians* g, void* ws, co
     a.target_bf16 = target_dtype == FH_BF16;
     const ViewTable vt = view_table(*p);
     prof_begin(FH_K_RENDER_BWD, s);
-    visit_stage(p, ws, s);
+    visit_stage(p, ws, VISITS_SORT, s);
     launch_bwd(p, ws, a, vt, true, s);
     prof_end(FH_K_RENDER_BWD, s);
     ReduceArgs r;

@@ -32,10 +32,32 @@ void device_exclusive_scan(const uint32_t* in, uint32_t* out, int64_t n, uint32_
                            hipStream_t s);
 int radix_sort(const uint32_t* keys_src, const uint32_t* vals_src, uint32_t* ka, uint32_t* va, uint32_t* kb,
                uint32_t* vb, bool with_vals, int64_t segs, int64_t seg_len, const unsigned long long* dev_len,
-               int64_t cap, int lo, int hi, uint32_t* hist, uint32_t* scan_tmp, hipStream_t s);
+               int64_t cap, int lo, int hi, uint32_t* hist, Counters* reset, hipStream_t s);
 size_t radix_hist_u32(int64_t segs, int64_t span);
+// rank tables, tiles per rank and their scan (sums and starts are set by the launch)
+struct RankArgs {
+    const uint32_t* order;
+    const int4* rect;
+    const float4* rec;
+    int64_t n, total, cap;
+    uint32_t *ntiles, *inst_off, *rank_of;
+    float4* rrec;
+    int rw;
+    Counters* counters;
+    uint32_t* ranges;          // nullable: cleared
+    int64_t n_ranges;
+    uint32_t *sums, *starts;
+    uint32_t n_starts;
+};
+void launch_ranks(const RankArgs& a, uint32_t* hist, uint32_t* scan_tmp, hipStream_t s);
+// first rank of k_duplicate's workgroups, as launch_ranks left them in hist
+inline const uint32_t* dup_starts(const uint32_t* hist, int64_t total) { return hist + (total + 1023) / 1024; }
+// voff = exclusive scan of the tiles' traversal lengths; the visit count and its overflow flag
+void launch_scan_visits(const uint32_t* niter, uint32_t* voff, int64_t n_tiles, uint32_t* scratch, Counters* c, int64_t cap,
+                        hipStream_t s);
 struct DupArgs {
     const uint32_t* inst_off;
+    const uint32_t* starts;
     const uint32_t* order;
     const int4* rect;
     int64_t n, total_ranks;
@@ -52,9 +74,6 @@ void launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t s);
 // (ranges) or the traversal length (tile_niter)
 void launch_tile_cost_keys(const uint32_t* ranges, const uint32_t* tile_niter, int64_t n_tiles, uint32_t* keys,
                            hipStream_t s);
-void launch_tiles_by_rank(const uint32_t* order, const int4* rect, int64_t n, int64_t total, uint32_t* ntiles,
-                          Counters* c, hipStream_t s);
-void launch_check_capacity(Counters* c, int64_t cap, hipStream_t s);
 void launch_duplicate(const DupArgs& a, hipStream_t s);
 void launch_ranges(const uint32_t* keys, const Counters* c, int64_t cap, int rank_bits, int packed, uint32_t* ranges,
                    hipStream_t s);
@@ -127,6 +146,10 @@ struct VisitStageArgs {
     uint32_t* vgid;     // [visits] its Gaussian
     float4* vrec;       // [visits * rw] its screen record
     int rw;             // float4 per record: 3 (Gaussians) or 4 (surfels)
+    uint32_t* vseg;            // nullable: cleared (n_vseg words)
+    int64_t n_vseg;
+    uint32_t* visited;         // nullable: cleared (n words)
+    int64_t n;
 };
 struct ReduceArgs {
     const uint32_t* order;
@@ -141,7 +164,7 @@ struct ReduceArgs {
     int64_t n, total;
     const float* part_geom;
     float* grad2d;
-    uint32_t* visited;         // [n] zeroed; bit v set for every visited (view v, Gaussian)
+    const uint32_t* visited;   // [n] bit v set for every visited (view v, Gaussian)
     const uint32_t* rank_of;
     const float* part_fuse;
     int d;
@@ -161,16 +184,14 @@ void launch_render_grad(const BwdArgs& a, const ViewTable& vt, int n_tiles, bool
 // sums, which the gradient kernel of the same call writes otherwise
 void launch_render_fuse(const BwdArgs& a, const ViewTable& vt, int n_tiles, bool bf16, bool ws, hipStream_t s);
 void launch_visit_stage(const VisitStageArgs& a, int n_tiles, hipStream_t s);
-void launch_vseg(const uint32_t* skeys, const Counters* c, int64_t cap, uint32_t* vseg, hipStream_t s);
-void launch_check_visits(const uint32_t* tile_voff, int n_tiles, Counters* c, int64_t cap, hipStream_t s);
+void launch_vseg(const uint32_t* skeys, const Counters* c, int64_t cap, uint32_t* vseg, const uint32_t* order, int64_t n,
+                 uint32_t* visited, hipStream_t s);
 // gp: floats per partial row, 12 (Gaussians: 10 used) or 16 (surfels: 14 used)
 void launch_reduce_geom(const ReduceArgs& a, int gp, hipStream_t s);
 void launch_reduce_fuse(const ReduceArgs& a, hipStream_t s);
 // units available for the long fusion reduction at a visit capacity (see reduce.hip)
 int64_t fuse_unit_capacity(int64_t visit_capacity);
 // rw: float4 per record (3, surfels 4)
-void launch_rank_tables(const uint32_t* order, const float4* rec, int64_t n, int64_t total, uint32_t* rank_of,
-                        float4* rrec, int rw, hipStream_t s);
 // ndfd.hip
 struct NdfdArgs {
     const uint32_t* tile_niter;

@@ -297,29 +297,6 @@ __global__ __launch_bounds__(256, 2) void k_render_fwd_f32(RenderArgs a, ViewTab
 }
 
 // ---------------------------------------------------------------------------
-// Per-tile traversal bookkeeping after the forward pass.
-__global__ void k_check_visits(const uint32_t* tile_voff, int n_tiles, Counters* c, int64_t cap) {
-    if (threadIdx.x == 0) {
-        const unsigned long long tot = tile_voff[n_tiles];
-        c->n_visited = tot;
-        c->visit_overflow = tot > (unsigned long long)cap ? 1u : 0u;
-    }
-}
-
-// Per depth rank j (view v = j / n): the rank of each (view, Gaussian) and the
-// screen records in rank order, so that a tile list entry (a rank) reaches its
-// record with one load.
-__global__ __launch_bounds__(256) void k_rank_tables(const uint32_t* __restrict__ order, const float4* __restrict__ rec,
-                                                     int64_t n, int64_t total, uint32_t* __restrict__ rank_of,
-                                                     float4* __restrict__ rrec, int rw) {
-    const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (j >= total) return;
-    const int64_t v = j / n;
-    const int64_t i = v * n + order[j];
-    rank_of[i] = (uint32_t)(j - v * n);
-    for (int k = 0; k < rw; ++k) rrec[rw * j + k] = rec[rw * i + k];
-}
-
 __global__ __launch_bounds__(256) void k_fuse_finalize(const float* sum, const float* comp, const float* wsum,
                                                        const float* wcomp, int64_t n, int d, const void* feat_in,
                                                        void* feat_out, int bf16) {
@@ -410,16 +387,6 @@ void launch_render_fwd_f32(const RenderArgs& a, const ViewTable& vt, int n_tiles
         launch_fwd_f32<true>(a, vt, n_tiles, s);
     else
         launch_fwd_f32<false>(a, vt, n_tiles, s);
-}
-
-void launch_check_visits(const uint32_t* tile_voff, int n_tiles, Counters* c, int64_t cap, hipStream_t s) {
-    hipLaunchKernelGGL(k_check_visits, dim3(1), dim3(64), 0, s, tile_voff, n_tiles, c, cap);
-}
-
-void launch_rank_tables(const uint32_t* order, const float4* rec, int64_t n, int64_t total, uint32_t* rank_of,
-                        float4* rrec, int rw, hipStream_t s) {
-    hipLaunchKernelGGL(k_rank_tables, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, order, rec, n, total,
-                       rank_of, rrec, rw);
 }
 
 void launch_fuse_finalize(const float* sum, const float* comp, const float* wsum, const float* wcomp, int64_t n, int d,
