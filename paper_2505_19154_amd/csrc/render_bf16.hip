@@ -13,22 +13,55 @@
 // Work mapping: one workgroup per (tile, group of ROWS pixel rows, channel
 // slice of DS); wave w is pixel row w of its group; lane l handles pixel
 // x = l % 16 and Gaussians 8 (l / 16) .. 8 (l / 16) + 7 of each 32-Gaussian
-// chunk.  The F accumulator takes DS / 4 registers per lane whatever ROWS is,
-// so 8-row (512-thread) workgroups, with twice the register budget of 16-row
-// ones, carry 256 channels and evaluate alpha once per pixel and Gaussian.  The lane's eight
-// weights are exactly its MFMA A-operand (rows = pixels, k = Gaussians).  The
-// four lanes of a pixel combine their transmittance with an exclusive product
-// scan, which reproduces the sequential walk (skip rule, stop rule) up to
-// rounding.
+// chunk.  The lane's eight weights are exactly its MFMA A-operand (rows =
+// pixels, k = Gaussians).  The four lanes of a pixel combine their
+// transmittance with an exclusive product scan, which reproduces the sequential
+// walk (skip rule, stop rule) up to rounding.  Features lie in LDS as they come,
+// a position's channels in a row, and reach the B operand by transposed reads
+// (writing them transposed took 16 two-byte stores a thread and chunk).
+//
+// Bound: VALU of the walk (62 % of the issue slots at 256 channels, matrix cores
+// 18 %), then the store of F.  256 channels, 500k Gaussians, 1920x1080, BF16 form:
+// 1.13 -> 0.79 ms, of which 0.34 is F at the HBM rate: a branch-free walk (1.13 ->
+// 1.02), four-row workgroups at three a CU with barriers of their own instead of
+// one of eight rows (0.86), and one multiply a feature row's address (0.79);
+// surfels 1.30 -> 0.88 ms; 128 channels, 1M Gaussians, 16 views 5.75 -> 4.75 ms.
+#include <type_traits>
+
 #include "kernels.hpp"
 
 namespace fh {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int FK = 32;        // Gaussians per chunk
-constexpr int FKP = 40;       // padded k-stride of the transposed feature tile (80 B rows)
+
+// LDS row of list position k of a chunk: positions 8 q + m (m < 4) in rows 4 q + m,
+// the others 16 rows on, so that the four lane groups of one transposed read take
+// sixteen consecutive rows (an odd multiple of 32 bytes apart: no bank conflicts).
+__device__ __forceinline__ int feat_row(int k) { return (k & 3) | ((k >> 1) & 12) | ((k & 4) << 2); }
+
+// Four rows (positions) by sixteen 16-bit columns (channels) per group of
+// sixteen lanes: lane i of a group gives the address of columns 4 (i % 4) of row
+// i / 4 and receives column i of the four rows.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+__device__ __forceinline__ bf16x8 read_tr(const unsigned char* at, int rows16) {
+    const uint2 lo = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)at));
+    const uint2 hi = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(at + rows16)));
+    return __builtin_bit_cast(bf16x8, u32x4{lo.x, lo.y, hi.x, hi.y});
+}
+
+// Two values rounded to BF16 (to nearest even), packed; and back.
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+}
+__device__ __forceinline__ float lo_f32(uint32_t p) { return __uint_as_float(p << 16); }
+__device__ __forceinline__ float hi_f32(uint32_t p) { return __uint_as_float(p & 0xFFFF0000u); }
 
 // Software pipeline over the tile's chunks of FK list positions.  While chunk
 // c is composited, threads 0..FK-1 hold in registers the list entries (depth
@@ -48,9 +81,9 @@ __device__ __forceinline__ uint32_t list_load(__amdgpu_buffer_rsrc_t rs, uint32_
 // l = bf16(x - h - m)) and F takes the six products hh, hm, mh, hl, lh, mm:
 // what is left out is below 2^-24 of w f, so F keeps FP32 accuracy on MFMA.
 template <int DS, int ROWS, bool FS, bool SURF>
-// (8-row shapes up to 128 channels keep four waves per SIMD: two workgroups per
-// CU; 4-row shapes are two or four workgroups per CU, each with its own barriers)
-__global__ __launch_bounds__(64 * ROWS, (ROWS <= 8 && DS <= 128 && !FS) ? 4 : (ROWS == 4 ? (SURF ? 3 : 2) : 1)) void k_render_fwd_bf16(
+// (shapes up to 128 channels keep four waves per SIMD, 4-row ones of 256 three:
+// several workgroups per CU, each with its own barriers)
+__global__ __launch_bounds__(64 * ROWS, (ROWS <= 8 && DS <= 128 && !FS) ? 4 : (ROWS == 4 ? 3 : 1)) void k_render_fwd_bf16(
     RenderArgs a, ViewTable vt) {
     constexpr int NB = DS / 16;
     static_assert(NB % 2 == 0, "channel blocks are processed in pairs");
@@ -63,7 +96,8 @@ __global__ __launch_bounds__(64 * ROWS, (ROWS <= 8 && DS <= 128 && !FS) ? 4 : (R
     __shared__ uint32_t sg[3][FK];
     constexpr int NFT = FS ? 3 : 1;                       // feature tiles: h (+ m, l)
     constexpr int NFR = FS ? 2 * NIT : NIT;               // 16-byte registers of one chunk's feature items
-    __shared__ __attribute__((aligned(16))) __bf16 sft[2][NFT * DS * FKP];
+    constexpr int FROW = 2 * DS + 32, FT = FK * FROW;     // bytes of a position's row, and of a feature tile
+    __shared__ __attribute__((aligned(16))) unsigned char sft[2][NFT * FT];
     __shared__ uint32_t smax[ROWS];
     __shared__ __attribute__((aligned(16))) uint8_t sbusy[2][16];   // per wave: a pixel still walking
     if (a.counters->inst_overflow) return;
@@ -94,7 +128,7 @@ __global__ __launch_bounds__(64 * ROWS, (ROWS <= 8 && DS <= 128 && !FS) ? 4 : (R
         // padding: opacity 0 never blends
         const RecT o = real ? r : pad_rec<SURF>();
         lds_put_prec<SURF, RG>(srec4[buf], k, o);
-        sg[buf][k] = real ? g : 0xFFFFFFFFu;
+        sg[buf][k] = real ? g : 0u;
     };
     // e: a raw list entry (masked here, where it is used, so that its load is
     // not waited for where it is issued)
@@ -103,60 +137,62 @@ __global__ __launch_bounds__(64 * ROWS, (ROWS <= 8 && DS <= 128 && !FS) ? 4 : (R
         r = load_rec<SURF>(a.rrec, j);
         g = a.order[j];
     };
-    // feature items of one chunk: item = k + FK * dg, 8 channels each; padding
-    // positions read Gaussian 0 and are zeroed when stored
-    auto load_feats = [&](const uint32_t* gl, uint4* fr) {
+    // feature items of one chunk, 8 channels each, the channels of a position
+    // consecutive; padding positions read Gaussian 0 and are zeroed when stored
+    auto load_feats = [&](const uint32_t* gl, u32x4* fr) {
 #pragma unroll
         for (int it = 0; it < NIT; ++it) {
             const int idx = (int)threadIdx.x + NT * it;
-            if (idx < FK * (DS / 8)) {
-                const int kk = idx % FK, dg = idx / FK;
-                const uint32_t g = gl[kk];
-                const uint32_t ga = g != 0xFFFFFFFFu ? g : 0u;
+            if ((it + 1) * NT <= FK * (DS / 8) || idx < FK * (DS / 8)) {
+                const int kk = idx / (DS / 8), dg = idx % (DS / 8);
+                const uint64_t row = (uint64_t)gl[kk] * (uint32_t)a.d;
                 if constexpr (FS) {
-                    const uint4* src = reinterpret_cast<const uint4*>(static_cast<const float*>(a.feat) +
-                                                                      (int64_t)ga * a.d + d0 + dg * 8);
+                    const u32x4* src =
+                        reinterpret_cast<const u32x4*>(static_cast<const float*>(a.feat) + row + (d0 + dg * 8));
                     fr[2 * it] = src[0];
                     fr[2 * it + 1] = src[1];
                 } else {
-                    fr[it] = *reinterpret_cast<const uint4*>(feat + (int64_t)ga * a.d + d0 + dg * 8);
+                    fr[it] = *reinterpret_cast<const u32x4*>(feat + row + (d0 + dg * 8));
                 }
             }
         }
     };
-    auto store_feats = [&](const uint32_t* gl, const uint4* fr, __bf16* dstb) {
-        uint16_t* dst = reinterpret_cast<uint16_t*>(dstb);
+    auto store_items = [&](auto whole, uint32_t pos, const u32x4* fr, unsigned char* dst) {
 #pragma unroll
         for (int it = 0; it < NIT; ++it) {
             const int idx = (int)threadIdx.x + NT * it;
-            if (idx < FK * (DS / 8)) {
-                const int kk = idx % FK, dg = idx / FK;
-                const bool pad = gl[kk] == 0xFFFFFFFFu;
+            if ((it + 1) * NT <= FK * (DS / 8) || idx < FK * (DS / 8)) {
+                const int kk = idx / (DS / 8), dg = idx % (DS / 8);
+                const bool pad = !decltype(whole)::value && pos + (uint32_t)kk >= len;
+                unsigned char* row = dst + feat_row(kk) * FROW + 16 * dg;
+                const u32x4 none = u32x4{0u, 0u, 0u, 0u};
                 if constexpr (FS) {
-                    const float4 f0 = __builtin_bit_cast(float4, fr[2 * it]);
-                    const float4 f1 = __builtin_bit_cast(float4, fr[2 * it + 1]);
-                    const float v[8] = {f0.x, f0.y, f0.z, f0.w, f1.x, f1.y, f1.z, f1.w};
+                    u32x4 h, m, l;
 #pragma unroll
-                    for (int m = 0; m < 8; ++m) {
-                        const float x = pad ? 0.0f : v[m];
-                        const __bf16 hb = (__bf16)x;
-                        const float r = x - (float)hb;
-                        const __bf16 mb = (__bf16)r;
-                        const __bf16 lb = (__bf16)(r - (float)mb);
-                        const int o = (dg * 8 + m) * FKP + kk;
-                        dst[o] = __builtin_bit_cast(uint16_t, hb);
-                        dst[DS * FKP + o] = __builtin_bit_cast(uint16_t, mb);
-                        dst[2 * DS * FKP + o] = __builtin_bit_cast(uint16_t, lb);
+                    for (int e = 0; e < 4; ++e) {
+                        const u32x4 f = pad ? none : fr[2 * it + e / 2];
+                        const float x0 = __uint_as_float(f[2 * (e % 2)]), x1 = __uint_as_float(f[2 * (e % 2) + 1]);
+                        h[e] = pack_bf16(x0, x1);
+                        const float r0 = x0 - lo_f32(h[e]), r1 = x1 - hi_f32(h[e]);
+                        m[e] = pack_bf16(r0, r1);
+                        l[e] = pack_bf16(r0 - lo_f32(m[e]), r1 - hi_f32(m[e]));
                     }
+                    *reinterpret_cast<u32x4*>(row) = h;
+                    *reinterpret_cast<u32x4*>(row + FT) = m;
+                    *reinterpret_cast<u32x4*>(row + 2 * FT) = l;
                 } else {
-                    uint4 f = fr[it];
-                    if (pad) f = make_uint4(0, 0, 0, 0);
-                    const uint16_t* h = reinterpret_cast<const uint16_t*>(&f);
-#pragma unroll
-                    for (int m = 0; m < 8; ++m) dst[(dg * 8 + m) * FKP + kk] = h[m];
+                    *reinterpret_cast<u32x4*>(row) = pad ? none : fr[it];
                 }
             }
         }
+    };
+
+    // (pos: the chunk's first list position; only the last chunk holds padding)
+    auto store_feats = [&](uint32_t pos, const u32x4* fr, unsigned char* dst) {
+        if (pos + FK <= len)
+            store_items(std::true_type{}, pos, fr, dst);
+        else
+            store_items(std::false_type{}, pos, fr, dst);
     };
 
     // prologue: chunks 0 and 1 into LDS, chunk 2's ranks into registers, then chunk 0's features
@@ -175,9 +211,9 @@ __global__ __launch_bounds__(64 * ROWS, (ROWS <= 8 && DS <= 128 && !FS) ? 4 : (R
     if (threadIdx.x < 32) reinterpret_cast<uint8_t*>(sbusy)[threadIdx.x] = 0;
     __syncthreads();
     if (len > 0) {   // (an empty list stages nothing: sg holds no Gaussians then)
-        uint4 fr[NFR];
+        u32x4 fr[NFR];
         load_feats(sg[0], fr);
-        store_feats(sg[0], fr, sft[0]);
+        store_feats(0u, fr, sft[0]);
     }
     __syncthreads();
 
@@ -198,84 +234,74 @@ __global__ __launch_bounds__(64 * ROWS, (ROWS <= 8 && DS <= 128 && !FS) ? 4 : (R
             get_rec(rk2, r2, g2);
             rk3 = list_load(list_rs, cpos + (uint32_t)(3 * FK + k));
         }
-        uint4 fr[NFR];
+        u32x4 fr[NFR];
         load_feats(sg[n3], fr);
 
-        // alpha of this lane's eight Gaussians and their transmittance product
+        // alpha of this lane's eight Gaussians (zero where they do not blend, and in
+        // a pixel that has stopped) and their transmittance product
+        const float least = done ? 2.0f : ALPHA_MIN;
         float al[8];
         float P = 1.0f;
 #pragma unroll
         for (int m = 0; m < 8; ++m) {
             const float alpha = prim_alpha<SURF>(lds_prec<SURF, RG>(srec4[b3], 8 * q + m), x, y);
-            al[m] = alpha >= ALPHA_MIN ? alpha : 0.0f;
+            al[m] = alpha >= least ? alpha : 0.0f;
             P *= (1.0f - al[m]);
         }
         const Rows4 Pr = rows4(P);
-        const float P0 = Pr.r0, P1 = Pr.r1, P2 = Pr.r2;
-        const float excl = q == 0 ? 1.0f : (q == 1 ? P0 : (q == 2 ? P0 * P1 : (P0 * P1) * P2));
-        float Tl = T * excl;
-        bool dl = done || Tl < T_MIN;
-        bool term = false;
+        float excl = q > 0 ? Pr.r0 : 1.0f;
+        excl = q > 1 ? excl * Pr.r1 : excl;
+        excl = q > 2 ? excl * Pr.r2 : excl;
+        // The walk.  Tv runs on past the stop (it never rises again), so that a
+        // Gaussian blends exactly where Tv behind it is at least T_MIN; Tl stays at
+        // the last such value.  W (this lane's 8 weights) goes straight into its
+        // MFMA A operand as BF16 hi + lo (FS: three terms).
+        float Tl = T * excl, Tv = Tl;
+        const bool open = Tl >= T_MIN;
         uint32_t mylast = 0;
-        // W (this lane's 8 weights) goes straight into its MFMA A operand as BF16 hi + lo
-        bf16x8 ahi, alo, amid;   // (amid: FS only; then alo holds the third term)
+        u32x4 whi, wlo, wmid;
+        auto colour = [&](int m) { return srec4[b3][prec_slot<SURF, RG>(8 * q + m) + 2]; };   // (opacity, r, g, b)
+        float4 col[2] = {colour(0), colour(1)};
 #pragma unroll
-        for (int m = 0; m < 8; ++m) {
-            // Both forms of the step give the same bits (colour by explicit
-            // fused multiply-adds; a Gaussian that does not blend adds w = 0
-            // exactly).  The branch-free form needs more registers than the
-            // shapes that keep four waves per SIMD have.
-            float wv = 0.0f;
-            const float4 col = srec4[b3][prec_slot<SURF, RG>(8 * q + m) + 2];   // (opacity, r, g, b)
-            if constexpr (ROWS == 8 && DS > 128) {
-                const float Tn = Tl * (1.0f - al[m]);
-                const bool act = !dl && al[m] > 0.0f;
-                const bool stop = act && Tn < T_MIN;
-                const bool blend = act && !stop;
-                wv = blend ? al[m] * Tl : 0.0f;
-                c0 = __builtin_fmaf(wv, col.y, c0);
-                c1 = __builtin_fmaf(wv, col.z, c1);
-                c2 = __builtin_fmaf(wv, col.w, c2);
-                Tl = blend ? Tn : Tl;
-                mylast = blend ? cpos + 8 * q + m + 1 : mylast;
-                dl = dl || stop;
-                term = term || stop;
-            } else {
-                if (!dl && al[m] > 0.0f) {
-                    const float Tn = Tl * (1.0f - al[m]);
-                    if (Tn < T_MIN) {
-                        dl = true;
-                        term = true;
-                    } else {
-                        wv = al[m] * Tl;
-                        c0 = __builtin_fmaf(wv, col.y, c0);
-                        c1 = __builtin_fmaf(wv, col.z, c1);
-                        c2 = __builtin_fmaf(wv, col.w, c2);
-                        Tl = Tn;
-                        mylast = cpos + 8 * q + m + 1;
-                    }
-                }
+        for (int m = 0; m < 8; m += 2) {
+            float4 next[2];
+            if (m < 6) {
+                next[0] = colour(m + 2);
+                next[1] = colour(m + 3);
             }
-            const __bf16 h = (__bf16)wv;
-            ahi[m] = h;
+            float wv[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const float Tn = Tv * (1.0f - al[m + e]);
+                const bool on = Tn >= T_MIN;
+                wv[e] = on ? al[m + e] * Tv : 0.0f;
+                Tl = on ? Tn : Tl;
+                Tv = Tn;
+                c0 = __builtin_fmaf(wv[e], col[e].y, c0);
+                c1 = __builtin_fmaf(wv[e], col[e].z, c1);
+                c2 = __builtin_fmaf(wv[e], col[e].w, c2);
+                mylast = wv[e] > 0.0f ? cpos + 8 * q + m + e + 1 : mylast;
+            }
+            uint32_t h = pack_bf16(wv[0], wv[1]);
+            const float r0 = wv[0] - lo_f32(h), r1 = wv[1] - hi_f32(h);
+            uint32_t r = pack_bf16(r0, r1);
             if constexpr (FS) {
-                const float r = wv - (float)h;
-                const __bf16 mb = (__bf16)r;
-                amid[m] = mb;
-                alo[m] = (__bf16)(r - (float)mb);
-            } else {
-                alo[m] = (__bf16)(wv - (float)h);
+                wmid[m / 2] = r;
+                r = pack_bf16(r0 - lo_f32(r), r1 - hi_f32(r));
             }
+            // (in order: the next pair's colours in flight, no more held)
+            asm volatile("" : "+v"(Tv), "+v"(c0), "+v"(c1), "+v"(c2), "+v"(h), "+v"(r), "+v"(mylast)::"memory");
+            whi[m / 2] = h;
+            wlo[m / 2] = r;
+            col[0] = next[0];
+            col[1] = next[1];
         }
-        // pixel state after the chunk: the first lane that stopped, else lane 3
-        const uint64_t tb = ballot64(term);
-        const Rows4 Tr = rows4(Tl);
-        const float Tq0 = Tr.r0, Tq1 = Tr.r1, Tq2 = Tr.r2, Tq3 = Tr.r3;
-        const bool t0 = (tb >> xi) & 1, t1 = (tb >> (xi + 16)) & 1, t2 = (tb >> (xi + 32)) & 1,
-                   t3 = (tb >> (xi + 48)) & 1;
+        const bf16x8 ahi = __builtin_bit_cast(bf16x8, whi), alo = __builtin_bit_cast(bf16x8, wlo);
+        // pixel state after the chunk: the first lane that stopped (its sign), else lane 3
+        const Rows4 Tr = rows4(open && Tv < T_MIN ? -Tl : Tl);
         if (!done) {
-            T = t0 ? Tq0 : (t1 ? Tq1 : (t2 ? Tq2 : Tq3));
-            done = t0 || t1 || t2 || t3;
+            T = fabsf(Tr.r0 < 0.0f ? Tr.r0 : (Tr.r1 < 0.0f ? Tr.r1 : (Tr.r2 < 0.0f ? Tr.r2 : Tr.r3)));
+            done = fminf(fminf(Tr.r0, Tr.r1), fminf(Tr.r2, Tr.r3)) < 0.0f;
         }
         const Rows4 Lr = rows4(__uint_as_float(mylast));
         const uint32_t lm = max(max(__float_as_uint(Lr.r0), __float_as_uint(Lr.r1)),
@@ -286,17 +312,14 @@ __global__ __launch_bounds__(64 * ROWS, (ROWS <= 8 && DS <= 128 && !FS) ? 4 : (R
         // lo products of one block are not issued back to back)
 #pragma unroll
         for (int j = 0; j < NB; j += 2) {
-            const bf16x8 bv0 = *reinterpret_cast<const bf16x8*>(&sft[b2][(j * 16 + xi) * FKP + 8 * q]);
-            const bf16x8 bv1 = *reinterpret_cast<const bf16x8*>(&sft[b2][((j + 1) * 16 + xi) * FKP + 8 * q]);
+            if (j % 4 == 0) asm volatile("" ::: "memory");
+            const unsigned char* fb = sft[b2] + (4 * q + (xi >> 2)) * FROW + 32 * j + 8 * (xi & 3);
+            const bf16x8 bv0 = read_tr(fb, 16 * FROW), bv1 = read_tr(fb + 32, 16 * FROW);
             if constexpr (FS) {
                 // the six products, smallest first: lh, hl, mm, mh, hm, hh
-                const bf16x8 bm0 = *reinterpret_cast<const bf16x8*>(&sft[b2][DS * FKP + (j * 16 + xi) * FKP + 8 * q]);
-                const bf16x8 bm1 =
-                    *reinterpret_cast<const bf16x8*>(&sft[b2][DS * FKP + ((j + 1) * 16 + xi) * FKP + 8 * q]);
-                const bf16x8 bl0 =
-                    *reinterpret_cast<const bf16x8*>(&sft[b2][2 * DS * FKP + (j * 16 + xi) * FKP + 8 * q]);
-                const bf16x8 bl1 =
-                    *reinterpret_cast<const bf16x8*>(&sft[b2][2 * DS * FKP + ((j + 1) * 16 + xi) * FKP + 8 * q]);
+                const bf16x8 amid = __builtin_bit_cast(bf16x8, wmid);
+                const bf16x8 bm0 = read_tr(fb + FT, 16 * FROW), bm1 = read_tr(fb + FT + 32, 16 * FROW);
+                const bf16x8 bl0 = read_tr(fb + 2 * FT, 16 * FROW), bl1 = read_tr(fb + 2 * FT + 32, 16 * FROW);
                 f32x4 s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(alo, bv0, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
                 f32x4 s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(alo, bv1, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
                 s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ahi, bl0, s0, 0, 0, 0);
@@ -317,7 +340,7 @@ __global__ __launch_bounds__(64 * ROWS, (ROWS <= 8 && DS <= 128 && !FS) ? 4 : (R
             }
         }
         // chunk c+1's features and chunk c+2's records to LDS
-        store_feats(sg[n3], fr, sft[b2 ^ 1]);
+        store_feats(cpos + FK, fr, sft[b2 ^ 1]);
         if (k < FK) {
             put_rec(nn3, cpos + (uint32_t)(2 * FK + k), r2, g2);
             rk2 = rk3;
@@ -407,10 +430,14 @@ static void launch_fwd_mfma(const RenderArgs& a, const ViewTable& vt, int n_tile
         }
         return;
     }
+    // 16 rows: one workgroup at 128 channels; narrower slices in four of four rows,
+    // whose records and features are cheap to stage four times and whose list
+    // latencies overlap (32 channels at 637x479 95 -> 72 us, 64 FP32 channels at
+    // 800x800 243 -> 202 us against one workgroup of 16 waves)
     switch (slice) {
-        case 32: hipLaunchKernelGGL((k_render_fwd_bf16<32, 16, FS, SURF>), g16, dim3(1024), 0, s, a, vt); break;
-        case 64: hipLaunchKernelGGL((k_render_fwd_bf16<64, 16, FS, SURF>), g16, dim3(1024), 0, s, a, vt); break;
-        case 96: hipLaunchKernelGGL((k_render_fwd_bf16<96, 16, FS, SURF>), g16, dim3(1024), 0, s, a, vt); break;
+        case 32: hipLaunchKernelGGL((k_render_fwd_bf16<32, 4, FS, SURF>), g4, dim3(256), 0, s, a, vt); break;
+        case 64: hipLaunchKernelGGL((k_render_fwd_bf16<64, 4, FS, SURF>), g4, dim3(256), 0, s, a, vt); break;
+        case 96: hipLaunchKernelGGL((k_render_fwd_bf16<96, 4, FS, SURF>), g4, dim3(256), 0, s, a, vt); break;
         default:
             // (16 rows of 128 channels is not an FP32-feature shape: it would spill)
             if constexpr (!FS) hipLaunchKernelGGL((k_render_fwd_bf16<128, 16, false, SURF>), g16, dim3(1024), 0, s, a, vt);
