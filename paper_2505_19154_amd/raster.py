@@ -467,9 +467,24 @@ class Rasterizer:
                 for i in range(n.value)]
 
     def forward(self, g: Gaussians, margin: float = 1.05) -> Image:
-        """prepare + render_fwd, growing the visit capacity until it fits."""
-        self.prepare(g, margin)
+        """prepare + render_fwd, growing the capacities until they fit."""
         img = None
+        if self.plan.inst_capacity > 0 and self.plan.visit_capacity > 0:
+            # Capacities of an earlier call mostly fit: the whole pass is queued and
+            # the counters are read once, after it (reading them before the
+            # compositing as well left the device idle for 80 to 100 us).  After an
+            # instance overflow the compositing kernels return at once.
+            self.project(g)
+            self.bin_sort()
+            img = self.render_fwd(g)
+            c = self.counters()
+            if not c.inst_overflow and not c.visit_overflow:
+                return img
+            if c.inst_overflow:
+                self._plan(int(c.n_instances * margin) + 1024, self.plan.visit_capacity)
+            else:
+                self._plan(self.plan.inst_capacity, max(int(c.n_visited * margin) + 1024, 1024))
+        self.prepare(g, margin)
         while True:
             img = self.render_fwd(g, img)
             c = self.counters()
