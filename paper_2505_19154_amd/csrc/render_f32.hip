@@ -6,10 +6,11 @@
 //   alpha = min(0.99, o G), skip if alpha < 1/255, stop before T drops below
 //   1e-4, w = alpha T, C += w rgb, F += w f, T *= (1 - alpha).
 //
+#include <type_traits>
+
 #include "kernels.hpp"
 
 namespace fh {
-
 
 __device__ __forceinline__ uint32_t inst_rank(const uint32_t* keys, const uint32_t* vals, int64_t i, int rank_bits,
                                               int packed) {
@@ -21,6 +22,17 @@ __device__ __forceinline__ float load_feat(const void* f, int bf16, int64_t idx)
 }
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+}
+__device__ __forceinline__ float lo_f32(uint32_t p) { return __uint_as_float(p << 16); }
+__device__ __forceinline__ float hi_f32(uint32_t p) { return __uint_as_float(p & 0xFFFF0000u); }
 
 // One 256-thread workgroup per (tile, slice of 16 NB channels); wave w owns the
 // pixel rows 4 w .. 4 w + 3, one pixel per lane.  The walk is sequential per
@@ -35,22 +47,31 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // chunks ahead (as in render_bf16.hip).  Bound: VALU work of the walk (about 30
 // instructions per pixel and position), then the FP32 matrix rate at 256
 // channels.  Against the VALU form: 500k, 1920x1080, D = 256 (BF16 storage)
-// 5.57 -> 2.50 ms; 150k, 987x657, D = 0 123 -> 88 us; 1k, 128x128, D = 16 69 ->
-// 54 us.
-template <int NB, bool SURF>
+// 5.57 -> 2.50 ms; 150k, 987x657, D = 0 123 -> 86 us; 1k, 128x128, D = 16 69 ->
+// 45 us.
+//
+// FB: features stored in BF16.  They enter v_mfma_f32_16x16x32_bf16 as stored and
+// W as three BF16 terms (h + m + l: exact, three roundings to 8 bits cover 24), 32
+// positions at once, so that only the FP32 accumulation rounds: 48 cycles for 32
+// positions of a 16 x 16 block where the FP32 instruction takes 256 (D = 256 above
+// 2.50 -> 1.36 ms).  Features stay in rows of positions in LDS (32 (NB | 1) bytes
+// apart, position 8 q + m in row 4 q + m or 16 + 4 q + m - 4) and are read transposed.
+template <int NB, bool FB, bool SURF>
 __global__ __launch_bounds__(256, 2) void k_render_fwd_f32(RenderArgs a, ViewTable vt, int vec) {
     using RecT = typename PrimRec<SURF>::T;
     constexpr int FK = 32;                               // positions per chunk
     constexpr int DS = 16 * NB;
     constexpr int FST = DS % 32 == 0 ? DS + 16 : DS;     // feature row stride: lanes q (rows apart) 16 dwords apart mod 64
-    constexpr int WST = 64 + 16;                         // weight row stride, the same
+    constexpr int WST = FB ? 66 : 64 + 16;               // weight row stride, the same (FB: lanes q are 8 rows apart)
+    constexpr int WROWS = FB ? FK : 16;
+    constexpr int FROW = 32 * (NB | 1);                  // FB: bytes of a feature row
     constexpr int GE = 4;                                // positions evaluated ahead of the walk
     constexpr int NG = NB > 0 ? 4 * NB : 1;              // four-channel items per feature row
     constexpr int ITEMS = NB > 0 ? FK * NG : 0, NI = NB > 0 ? (ITEMS + 255) / 256 : 1;
     __shared__ RecT srec[3][FK];
     __shared__ uint32_t sg[3][FK];
-    __shared__ __attribute__((aligned(16))) float sft[NB > 0 ? 2 * FK * FST : 4];
-    __shared__ float sw[NB > 0 ? 4 * 16 * WST : 4];
+    __shared__ __attribute__((aligned(16))) float sft[NB > 0 ? (FB ? 2 * FK * FROW / 4 : 2 * FK * FST) : 4];
+    __shared__ float sw[NB > 0 ? 4 * WROWS * WST : 4];
     __shared__ uint32_t smax[4], sodd;
     __shared__ uint8_t sbusy[2][4];
     if (a.counters->inst_overflow) return;
@@ -76,27 +97,24 @@ __global__ __launch_bounds__(256, 2) void k_render_fwd_f32(RenderArgs a, ViewTab
         srec[buf][k] = real ? r : pad_rec<SURF>();   // padding: opacity 0 never blends
         sg[buf][k] = real ? g : 0xFFFFFFFFu;
     };
-    auto load_feats = [&](const uint32_t* gl, float4* fr) {
+    using Item = typename std::conditional<FB, uint2, float4>::type;   // four channels as stored
+    auto load_feats = [&](const uint32_t* gl, Item* fr) {
 #pragma unroll
         for (int it = 0; it < NI; ++it) {
             const int idx = (int)threadIdx.x + 256 * it;
-            fr[it] = make_float4(0.f, 0.f, 0.f, 0.f);
+            fr[it] = Item{};
             if (idx < ITEMS) {
                 const uint32_t g = gl[idx / NG];
                 const int c = d0 + 4 * (idx % NG);
                 if (g != 0xFFFFFFFFu) {
-                    if (a.feat_bf16) {
+                    if constexpr (FB) {
                         const uint16_t* f = static_cast<const uint16_t*>(a.feat) + (int64_t)g * a.d;
                         if (vec) {
-                            if (c < a.d) {
-                                const uint2 u = *reinterpret_cast<const uint2*>(f + c);
-                                fr[it] = make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xFFFF0000u),
-                                                     __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xFFFF0000u));
-                            }
+                            if (c < a.d) fr[it] = *reinterpret_cast<const uint2*>(f + c);
                         } else {
-                            fr[it] = make_float4(c < a.d ? bf16_to_f32(f[c]) : 0.f, c + 1 < a.d ? bf16_to_f32(f[c + 1]) : 0.f,
-                                                 c + 2 < a.d ? bf16_to_f32(f[c + 2]) : 0.f,
-                                                 c + 3 < a.d ? bf16_to_f32(f[c + 3]) : 0.f);
+                            const uint32_t e0 = c < a.d ? f[c] : 0u, e1 = c + 1 < a.d ? f[c + 1] : 0u;
+                            const uint32_t e2 = c + 2 < a.d ? f[c + 2] : 0u, e3 = c + 3 < a.d ? f[c + 3] : 0u;
+                            fr[it] = make_uint2(e0 | (e1 << 16), e2 | (e3 << 16));
                         }
                     } else {
                         const float* f = static_cast<const float*>(a.feat) + (int64_t)g * a.d;
@@ -113,20 +131,35 @@ __global__ __launch_bounds__(256, 2) void k_render_fwd_f32(RenderArgs a, ViewTab
     };
     // (a feature that is not finite enters the contraction as zero, 0 * inf must
     // not reach the pixels that do not blend it, and is added at the end)
-    auto store_feats = [&](const float4* fr, int buf) {
+    auto store_feats = [&](const Item* fr, int buf) {
 #pragma unroll
         for (int it = 0; it < NI; ++it) {
             const int idx = (int)threadIdx.x + 256 * it;
             if (idx < ITEMS) {
-                float4 f = fr[it];
-                if (!(isfinite(f.x) && isfinite(f.y) && isfinite(f.z) && isfinite(f.w))) {
-                    sodd = 1u;
-                    f.x = isfinite(f.x) ? f.x : 0.0f;
-                    f.y = isfinite(f.y) ? f.y : 0.0f;
-                    f.z = isfinite(f.z) ? f.z : 0.0f;
-                    f.w = isfinite(f.w) ? f.w : 0.0f;
+                const int kk = idx / NG, cg = idx % NG;
+                if constexpr (FB) {
+                    uint2 f = fr[it];
+                    const uint32_t EXP = 0x7F80u;
+                    const bool o0 = (f.x & EXP) == EXP, o1 = ((f.x >> 16) & EXP) == EXP;
+                    const bool o2 = (f.y & EXP) == EXP, o3 = ((f.y >> 16) & EXP) == EXP;
+                    if (o0 || o1 || o2 || o3) {
+                        sodd = 1u;
+                        f.x &= (o0 ? 0u : 0xFFFFu) | (o1 ? 0u : 0xFFFF0000u);
+                        f.y &= (o2 ? 0u : 0xFFFFu) | (o3 ? 0u : 0xFFFF0000u);
+                    }
+                    const int row = (kk & 3) | ((kk >> 1) & 12) | ((kk & 4) << 2);
+                    *reinterpret_cast<uint2*>(reinterpret_cast<unsigned char*>(sft) + (buf * FK + row) * FROW + 8 * cg) = f;
+                } else {
+                    float4 f = fr[it];
+                    if (!(isfinite(f.x) && isfinite(f.y) && isfinite(f.z) && isfinite(f.w))) {
+                        sodd = 1u;
+                        f.x = isfinite(f.x) ? f.x : 0.0f;
+                        f.y = isfinite(f.y) ? f.y : 0.0f;
+                        f.z = isfinite(f.z) ? f.z : 0.0f;
+                        f.w = isfinite(f.w) ? f.w : 0.0f;
+                    }
+                    *reinterpret_cast<float4*>(&sft[buf * FK * FST + kk * FST + 4 * cg]) = f;
                 }
-                *reinterpret_cast<float4*>(&sft[buf * FK * FST + (idx / NG) * FST + 4 * (idx % NG)]) = f;
             }
         }
     };
@@ -147,7 +180,7 @@ __global__ __launch_bounds__(256, 2) void k_render_fwd_f32(RenderArgs a, ViewTab
     }
     __syncthreads();
     if (NB > 0 && len > 0) {
-        float4 fr[NI];
+        Item fr[NI];
         load_feats(sg[0], fr);
         store_feats(fr, 0);
     }
@@ -158,10 +191,12 @@ __global__ __launch_bounds__(256, 2) void k_render_fwd_f32(RenderArgs a, ViewTab
     for (int pb = 0; pb < 4; ++pb)
 #pragma unroll
         for (int j = 0; j < NB; ++j) acc[pb][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float T = 1.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f;
-    bool done = !inside, wave_done = ballot64(inside) == 0;
+    // Tv runs on past the stop (it never rises again), so that a Gaussian blends
+    // exactly where Tv behind it is at least T_MIN; T stays at the last such value
+    float T = 1.0f, Tv = inside ? 1.0f : 0.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f;
+    bool wave_done = ballot64(inside) == 0;
     uint32_t last = 0;
-    float* wsw = sw + w * 16 * WST;
+    float* wsw = sw + w * WROWS * WST;
 
     int b3 = 0, b2 = 0;   // chunk index mod 3 and mod 2
     for (uint32_t cpos = 0; cpos < len; cpos += FK) {
@@ -172,7 +207,7 @@ __global__ __launch_bounds__(256, 2) void k_render_fwd_f32(RenderArgs a, ViewTab
             get_rec(rk2, r2, g2);
             rk3 = rank_at(cpos + (uint32_t)(3 * FK + k));
         }
-        float4 fr[NI];
+        Item fr[NI];
         if constexpr (NB > 0) load_feats(sg[n3], fr);
 
         if (!wave_done) {
@@ -188,23 +223,33 @@ __global__ __launch_bounds__(256, 2) void k_render_fwd_f32(RenderArgs a, ViewTab
 #pragma unroll
                     for (int m = 0; m < GE; ++m) {
                         const float4 col = rp[m].r2;   // (opacity, r, g, b)
-                        const float Tn = T * (1.0f - al[m]);
-                        const bool act = !done && !(al[m] < ALPHA_MIN);
-                        const bool stop = act && Tn < T_MIN;
-                        const bool blend = act && !stop;
-                        const float wv = blend ? al[m] * T : 0.0f;
+                        float Tn, wv;
+                        bool on, blend;
+                        if constexpr (NB == 0) {   // (flags cost less than the extra selects: 90 against 97 us)
+                            const bool act = Tv >= T_MIN && !(al[m] < ALPHA_MIN);
+                            Tn = Tv * (1.0f - al[m]);
+                            on = blend = act && !(Tn < T_MIN);
+                            wv = al[m] * Tv;
+                            Tn = act ? Tn : Tv;
+                        } else {
+                            const float am = al[m] < ALPHA_MIN ? 0.0f : al[m];
+                            Tn = Tv * (1.0f - am);
+                            on = Tn >= T_MIN;
+                            wv = on ? am * Tv : 0.0f;
+                            blend = wv > 0.0f;
+                        }
                         if (blend) {
                             c0 = __builtin_fmaf(wv, col.y, c0);
                             c1 = __builtin_fmaf(wv, col.z, c1);
                             c2 = __builtin_fmaf(wv, col.w, c2);
                         }
-                        T = blend ? Tn : T;
+                        T = on ? Tn : T;
+                        Tv = Tn;
                         last = blend ? cpos + (uint32_t)(16 * half + grp + m + 1) : last;
-                        done = done || stop;
-                        if constexpr (NB > 0) wsw[(grp + m) * WST + lane] = wv;
+                        if constexpr (NB > 0) wsw[((FB ? 16 * half : 0) + grp + m) * WST + lane] = wv;
                     }
                 }
-                if constexpr (NB > 0) {
+                if constexpr (NB > 0 && !FB) {
                     const float* sf = sft + b2 * FK * FST + 16 * half * FST;
 #pragma unroll
                     for (int st = 0; st < 4; ++st) {
@@ -221,7 +266,41 @@ __global__ __launch_bounds__(256, 2) void k_render_fwd_f32(RenderArgs a, ViewTab
                     }
                 }
             }
-            wave_done = ballot64(!done) == 0;
+            if constexpr (NB > 0 && FB) {
+                bf16x8 aw[3][4];   // W of pixel (row 4 w + pb, column xi), positions 8 q .. 8 q + 7
+#pragma unroll
+                for (int pb = 0; pb < 4; ++pb) {
+                    u32x4 h, m, l;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float* wp = wsw + (8 * q + 2 * e) * WST + 16 * pb + xi;
+                        const float x0 = wp[0], x1 = wp[WST];
+                        h[e] = pack_bf16(x0, x1);
+                        const float r0 = x0 - lo_f32(h[e]), r1 = x1 - hi_f32(h[e]);
+                        m[e] = pack_bf16(r0, r1);
+                        l[e] = pack_bf16(r0 - lo_f32(m[e]), r1 - hi_f32(m[e]));
+                    }
+                    aw[0][pb] = __builtin_bit_cast(bf16x8, h);
+                    aw[1][pb] = __builtin_bit_cast(bf16x8, m);
+                    aw[2][pb] = __builtin_bit_cast(bf16x8, l);
+                }
+                const unsigned char* fb = reinterpret_cast<const unsigned char*>(sft) +
+                                          (b2 * FK + 4 * q + (xi >> 2)) * FROW + 8 * (xi & 3);
+                typedef __attribute__((address_space(3))) s16x4 lds4;
+#pragma unroll
+                for (int j = 0; j < NB; ++j) {
+                    const uint2 lo = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4*)(fb + 32 * j)));
+                    const uint2 hi =
+                        __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4*)(fb + 16 * FROW + 32 * j)));
+                    const bf16x8 f = __builtin_bit_cast(bf16x8, u32x4{lo.x, lo.y, hi.x, hi.y});
+#pragma unroll
+                    for (int c = 2; c >= 0; --c)   // (small terms first)
+#pragma unroll
+                        for (int pb = 0; pb < 4; ++pb)
+                            acc[pb][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aw[c][pb], f, acc[pb][j], 0, 0, 0);
+                }
+            }
+            wave_done = ballot64(Tv >= T_MIN) == 0;
         }
         // chunk c+1's features and chunk c+2's records to LDS
         if constexpr (NB > 0) store_feats(fr, b2 ^ 1);
@@ -365,21 +444,29 @@ __global__ __launch_bounds__(256) void k_fuse_finalize_rows(const float* __restr
 }
 
 // ---------------------------------------------------------------------------
-template <bool SURF>
+template <bool FB, bool SURF>
 static void launch_fwd_f32(const RenderArgs& a, const ViewTable& vt, int n_tiles, hipStream_t s) {
     // 16-byte (BF16: 8-byte) feature loads where every row is aligned to them
-    const int vec = a.d % 4 == 0 && reinterpret_cast<uintptr_t>(a.feat) % (a.feat_bf16 ? 8 : 16) == 0;
+    const int vec = a.d % 4 == 0 && reinterpret_cast<uintptr_t>(a.feat) % (FB ? 8 : 16) == 0;
     const unsigned ns = (unsigned)((a.d + 127) / 128);
-    if (a.d == 0)
-        hipLaunchKernelGGL((k_render_fwd_f32<0, SURF>), dim3(n_tiles, 1), dim3(256), 0, s, a, vt, vec);
-    else if (a.d <= 16)
-        hipLaunchKernelGGL((k_render_fwd_f32<1, SURF>), dim3(n_tiles, 1), dim3(256), 0, s, a, vt, vec);
+    if (a.d <= 16)
+        hipLaunchKernelGGL((k_render_fwd_f32<1, FB, SURF>), dim3(n_tiles, 1), dim3(256), 0, s, a, vt, vec);
     else if (a.d <= 32)
-        hipLaunchKernelGGL((k_render_fwd_f32<2, SURF>), dim3(n_tiles, 1), dim3(256), 0, s, a, vt, vec);
+        hipLaunchKernelGGL((k_render_fwd_f32<2, FB, SURF>), dim3(n_tiles, 1), dim3(256), 0, s, a, vt, vec);
     else if (a.d <= 64)
-        hipLaunchKernelGGL((k_render_fwd_f32<4, SURF>), dim3(n_tiles, 1), dim3(256), 0, s, a, vt, vec);
+        hipLaunchKernelGGL((k_render_fwd_f32<4, FB, SURF>), dim3(n_tiles, 1), dim3(256), 0, s, a, vt, vec);
     else
-        hipLaunchKernelGGL((k_render_fwd_f32<8, SURF>), dim3(n_tiles, ns), dim3(256), 0, s, a, vt, vec);
+        hipLaunchKernelGGL((k_render_fwd_f32<8, FB, SURF>), dim3(n_tiles, ns), dim3(256), 0, s, a, vt, vec);
+}
+
+template <bool SURF>
+static void launch_fwd_f32(const RenderArgs& a, const ViewTable& vt, int n_tiles, hipStream_t s) {
+    if (a.d == 0)
+        hipLaunchKernelGGL((k_render_fwd_f32<0, false, SURF>), dim3(n_tiles, 1), dim3(256), 0, s, a, vt, 0);
+    else if (a.feat_bf16)
+        launch_fwd_f32<true, SURF>(a, vt, n_tiles, s);
+    else
+        launch_fwd_f32<false, SURF>(a, vt, n_tiles, s);
 }
 
 void launch_render_fwd_f32(const RenderArgs& a, const ViewTable& vt, int n_tiles, hipStream_t s) {
