@@ -28,9 +28,9 @@
 //                                                          matrix, masked, hi + lo)
 // Accumulator layout and operand layout agree up to a permutation of the
 // contracted index, so the running vectors never leave registers: lane
-// (xi, q) of a 16-lane row holds channels 16 m + 4 q + r of pixel xi, which is
-// exactly the B operand of the slab 32 s .. 32 s + 31 when the A operand reads
-// its channels in the order (32 s + 4 q + r, 32 s + 16 + 4 q + r); and it walks
+// (xi, q) of a 16-lane row holds channels 32 s + 8 q .. + 7 of pixel xi in the
+// accumulators of blocks 2 s and 2 s + 1 (whose rows are taken in that order),
+// which is exactly the B operand of the slab 32 s .. 32 s + 31; and it walks
 // the positions 4 q + r and 16 + 4 q + r of the chunk, which are both the rows
 // the contractions return to it and the k-slots of its weight operand.
 //
@@ -44,6 +44,11 @@
 // kernel adds both halves into the gradient kernel's partials in a fixed
 // order.
 //
+// Bound: VALU (55 % of the issue slots at 256 channels, matrix cores 19 %) under
+// five barriers a chunk with one workgroup a CU (252 registers): 500k Gaussians,
+// 256 channels, 1920x1080, 4.70 -> 3.89 ms with the features staged once and read
+// transposed and the splits converted in pairs.
+//
 // SURF: the surfel primitive (Section 3.1): four-float4 records, alpha at the
 // ray-plane intersection, and per half the nine record entries' terms and
 // sum dL/dpower (rows of 16 floats), from the sums of dL/dk and dL/dk dx
@@ -54,9 +59,13 @@ namespace fh {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int NK = 32;                       // positions per chunk
-constexpr int NJP = 40;                      // row stride (bf16) of the transposed features and the Gram operands
+constexpr int NJP = 40;                      // row stride (bf16) of the Gram operands
 constexpr int NSK = NK + 3;                  // padded per-pixel stride of dL/dpower
 constexpr int NRG = 4;                       // record padding group (lane rows read records 4 apart)
 constexpr int NDFD_PARTS = 2;                // halves per visit in the partial array
@@ -74,13 +83,18 @@ __device__ __forceinline__ bf16x8 bf16x8_of(uint2 lo, uint2 hi) {
     return __builtin_bit_cast(bf16x8, make_uint4(lo.x, lo.y, hi.x, hi.y));
 }
 
+// v = h + l to about 16 significant bits, converted in pairs.
 __device__ __forceinline__ void split8(const float* v, bf16x8& h, bf16x8& l) {
+    u32x4 hp, lp;
 #pragma unroll
-    for (int m = 0; m < 8; ++m) {
-        const __bf16 hb = (__bf16)v[m];
-        h[m] = hb;
-        l[m] = (__bf16)(v[m] - (float)hb);
+    for (int e = 0; e < 4; ++e) {
+        const float x0 = v[2 * e], x1 = v[2 * e + 1];
+        hp[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x0, x1}, bf16x2));
+        const float r0 = x0 - __uint_as_float(hp[e] << 16), r1 = x1 - __uint_as_float(hp[e] & 0xFFFF0000u);
+        lp[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{r0, r1}, bf16x2));
     }
+    h = __builtin_bit_cast(bf16x8, hp);
+    l = __builtin_bit_cast(bf16x8, lp);
 }
 
 template <int D, bool GRAD, bool SURF>
@@ -93,11 +107,10 @@ __global__ __launch_bounds__(512) void k_ndfd(NdfdArgs a, ViewTable vt) {
     constexpr int NT = 64 * ROWS;             // threads
     constexpr int NS = D / 32;                // 32-channel slabs
     constexpr int NB = D / 16;                // 16-channel accumulator blocks
-    constexpr int DP = D + 8;                 // row stride (bf16) of the feature tile
+    constexpr int DP = D + 16;                // row stride (bf16) of the feature tile: an odd multiple of 32 bytes
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __bf16* sfeat = reinterpret_cast<__bf16*>(smem);          // [NK][DP]
-    __bf16* sfeatT = sfeat + NK * DP;                          // [D][NJP]
-    __bf16* sA = sfeatT + D * NJP;                             // [3 masks][hi, lo][NK][NJP]
+    __bf16* sA = sfeat + NK * DP;                              // [3 masks][hi, lo][NK][NJP]
     float* sG = reinterpret_cast<float*>(sA + 6 * NK * NJP);  // [NK][NK + 1]
     float* sinv = sG + NK * (NK + 1);                          // [NK]
     float* sdp = sinv + NK;                                    // [16 ROWS][NSK] dL/dpower (gradient)
@@ -132,7 +145,7 @@ __global__ __launch_bounds__(512) void k_ndfd(NdfdArgs a, ViewTable vt) {
         return;
     }
 
-    // F_gt of this lane's pixel, channels (32 s + 4 q + m, 32 s + 16 + 4 q + m):
+    // F_gt of this lane's pixel, channels 32 s + 8 q + m:
     // the B operand of phi; its norm over the pixel's four lanes
     bf16x8 gto[NS];
     float gn2 = 0.0f;
@@ -140,8 +153,8 @@ __global__ __launch_bounds__(512) void k_ndfd(NdfdArgs a, ViewTable vt) {
     for (int s = 0; s < NS; ++s) {
         uint2 lo = make_uint2(0u, 0u), hi = make_uint2(0u, 0u);
         if (inside) {
-            lo = *reinterpret_cast<const uint2*>(a.gt + p * D + 32 * s + 4 * q);
-            hi = *reinterpret_cast<const uint2*>(a.gt + p * D + 32 * s + 16 + 4 * q);
+            lo = *reinterpret_cast<const uint2*>(a.gt + p * D + 32 * s + 8 * q);
+            hi = *reinterpret_cast<const uint2*>(a.gt + p * D + 32 * s + 8 * q + 4);
         }
         gto[s] = bf16x8_of(lo, hi);
 #pragma unroll
@@ -213,35 +226,12 @@ __global__ __launch_bounds__(512) void k_ndfd(NdfdArgs a, ViewTable vt) {
     };
     auto commit = [&]() {
         if ((int)threadIdx.x < RD * NK) reinterpret_cast<float*>(srec)[4 * prec_slot<SURF, NRG>(rk) + rj] = prec;
-        // item = (position k, 8-channel group dg), k fastest.  The transposed
-        // tile is written in 4-byte words holding positions (2p, 2p + 1) of one
-        // channel: the neighbouring lane (k ^ 1, same dg) passes its row, the
-        // even lane writes channels 0-3 of the group and the odd lane 4-7, so
-        // that a store's four lane groups (even / odd, two dg) meet disjoint
-        // bank ranges (rows 8 channels apart are 160 words apart).
+        // item = (position k, 8-channel group dg), k fastest
         uint16_t* f16 = reinterpret_cast<uint16_t*>(sfeat);
-        uint32_t* ft32 = reinterpret_cast<uint32_t*>(sfeatT);
-        const bool odd = (kk & 1) != 0;
 #pragma unroll
         for (int it = 0; it < NI; ++it) {
             const int idx = threadIdx.x + NT * it;
-            // (every lane of a wave takes part in the exchange; NT is a multiple of 64)
-            const uint4 nb = make_uint4(__shfl_xor(praw[it].x, 1), __shfl_xor(praw[it].y, 1),
-                                        __shfl_xor(praw[it].z, 1), __shfl_xor(praw[it].w, 1));
-            if (idx < ITEMS) {
-                const int dg = idx / NK;
-                *reinterpret_cast<uint4*>(&f16[kk * DP + dg * 8]) = praw[it];
-                // words of channels 2j, 2j + 1 (j = 0, 1 even lanes; 2, 3 odd lanes)
-                const uint4 lo4 = odd ? nb : praw[it], hi4 = odd ? praw[it] : nb;   // positions 2p, 2p + 1
-                const uint32_t wl0 = odd ? lo4.z : lo4.x, wl1 = odd ? lo4.w : lo4.y;
-                const uint32_t wh0 = odd ? hi4.z : hi4.x, wh1 = odd ? hi4.w : hi4.y;
-                const int m0 = odd ? 4 : 0;
-                uint32_t* row = ft32 + (dg * 8 + m0) * (NJP / 2) + (kk >> 1);
-                row[0 * (NJP / 2)] = (wl0 & 0xFFFFu) | (wh0 << 16);
-                row[1 * (NJP / 2)] = (wl0 >> 16) | (wh0 & 0xFFFF0000u);
-                row[2 * (NJP / 2)] = (wl1 & 0xFFFFu) | (wh1 << 16);
-                row[3 * (NJP / 2)] = (wl1 >> 16) | (wh1 & 0xFFFF0000u);
-            }
+            if (idx < ITEMS) *reinterpret_cast<uint4*>(&f16[kk * DP + (idx / NK) * 8]) = praw[it];
         }
     };
     // first chunk of a pass in flight, the second one's Gaussians requested
@@ -256,18 +246,24 @@ __global__ __launch_bounds__(512) void k_ndfd(NdfdArgs a, ViewTable vt) {
         fetch_data(fwd, i + 1);
         fetch_gid(fwd, i + 2);
     };
-    // A operand of a contraction over channels: feature row `row`, slab s, in
-    // the channel order of the accumulator layout
+    // A operand of a contraction over channels: feature row `row`, channels
+    // 32 s + 8 q .. + 7
     auto featA = [&](int row, int s) -> bf16x8 {
-        const uint2 lo = *reinterpret_cast<const uint2*>(&sfeat[row * DP + 32 * s + 4 * q]);
-        const uint2 hi = *reinterpret_cast<const uint2*>(&sfeat[row * DP + 32 * s + 16 + 4 * q]);
-        return bf16x8_of(lo, hi);
+        return *reinterpret_cast<const bf16x8*>(&sfeat[row * DP + 32 * s + 8 * q]);
     };
-    // A operand of a contraction over positions: channel row d, positions
-    // (4 q + m, 16 + 4 q + m) -- this lane group's walked positions
-    auto featTA = [&](int d) -> bf16x8 {
-        const uint2 lo = *reinterpret_cast<const uint2*>(&sfeatT[d * NJP + 4 * q]);
-        const uint2 hi = *reinterpret_cast<const uint2*>(&sfeatT[d * NJP + 16 + 4 * q]);
+    // A operand of a contraction over positions (4 q + m, 16 + 4 q + m: this lane
+    // group's walked positions), by transposed reads of the same rows: lane 4 i +
+    // c of a group gives four channels of row i and receives, as row c' = lane of
+    // the block, one channel of the four rows.  Block 2 s + h takes channels 32 s +
+    // 8 (row / 4) + 4 h + row % 4, so that a lane's accumulators of blocks 2 s and
+    // 2 s + 1 are the channels featA pairs them with.  (The tile was written a
+    // second time, transposed, before: eight lane exchanges and eight stores a
+    // thread and chunk, and bank conflicts in 19 % of the cycles.)
+    auto featTA = [&](int mb) -> bf16x8 {
+        typedef __attribute__((address_space(3))) s16x4 lds4;
+        const __bf16* at = sfeat + (4 * q + (xi >> 2)) * DP + 32 * (mb >> 1) + 8 * (xi & 3) + 4 * (mb & 1);
+        const uint2 lo = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4*)at));
+        const uint2 hi = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4*)(at + 16 * DP)));
         return bf16x8_of(lo, hi);
     };
     // waves 0..3: the chunk's Gram matrix G[j][k] = f_j . f_k, one 16 x 16 block
@@ -339,7 +335,7 @@ __global__ __launch_bounds__(512) void k_ndfd(NdfdArgs a, ViewTable vt) {
     auto accumulate = [&](f32x4* acc, const bf16x8& vh, const bf16x8& vl) {
 #pragma unroll
         for (int mb = 0; mb < NB; ++mb) {
-            const bf16x8 fa = featTA(16 * mb + xi);
+            const bf16x8 fa = featTA(mb);
             acc[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, vh, acc[mb], 0, 0, 0);
             acc[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, vl, acc[mb], 0, 0, 0);
         }
@@ -705,7 +701,7 @@ __global__ __launch_bounds__(256) void k_ndfd_combine(const float* __restrict__ 
 template <int D, bool SURF>
 static void launch_ndfd_d(const NdfdArgs& a, const ViewTable& vt, int n_tiles, bool grad, hipStream_t s) {
     constexpr int ROWS = 8;
-    const size_t lds = sizeof(__bf16) * ((size_t)NK * (D + 8) + (size_t)D * NJP + 6 * (size_t)NK * NJP) +
+    const size_t lds = sizeof(__bf16) * ((size_t)NK * (D + 16) + 6 * (size_t)NK * NJP) +
                        sizeof(float) * ((size_t)NK * (NK + 1) + NK + (size_t)TILE * ROWS * NSK +
                                         (size_t)ROWS * NdfdPart<SURF>::NQ * NK);
     if (grad)
