@@ -85,23 +85,6 @@ __device__ __forceinline__ uint32_t wave_slot(unsigned int* counter, bool take) 
     return base + (uint32_t)__builtin_popcountll(m & lanemask_lt());
 }
 
-// The same for n slots per lane (n = 0 takes none): the lane's first slot.
-__device__ __forceinline__ uint32_t wave_slots(unsigned int* counter, uint32_t n) {
-    const int lane = lane_id();
-    uint32_t incl = n;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t y = (uint32_t)__shfl_up((int)incl, off, 64);
-        if (lane >= off) incl += y;
-    }
-    const uint32_t tot = (uint32_t)__shfl((int)incl, 63, 64);
-    if (tot == 0) return 0u;
-    uint32_t base = 0u;
-    if (lane == 63) base = atomicAdd(counter, tot);
-    base = (uint32_t)__shfl((int)base, 63, 64);
-    return base + incl - n;
-}
-
 // Partial rows of GP floats (Gaussians 12, 10 used; surfels 16, 14 used).
 template <int GP>
 __device__ __forceinline__ void add_geom(float* acc, const float* part_geom, uint32_t idx) {
@@ -294,9 +277,39 @@ __global__ __launch_bounds__(256) void k_fuse_classify(ReduceArgs a) {
     const uint32_t total = g < a.n ? fuse_visit_total(a, g) : 0u;
     const bool is_short = total > 0 && total <= LONG_FUSE, is_long = total > LONG_FUSE;
     const uint32_t nu = is_long ? (total + FUSE_UNIT - 1) / FUSE_UNIT : 0u;
-    const uint32_t sslot = wave_slot(&a.counters->n_short_fuse, is_short);
-    const uint32_t slot = wave_slot(&a.counters->n_long_fuse, is_long);
-    const uint32_t ub = wave_slots(&a.counters->n_fuse_units, nu);
+    // slots of the workgroup's lanes: prefixes within the wave and over the waves,
+    // one atomic a queue and workgroup (one a wave took most of the kernel: 8k to
+    // 16k waves on the same three words)
+    __shared__ uint32_t sums[3][4], bases[3];
+    const int lane = lane_id(), w = (int)threadIdx.x >> 6;
+    const uint64_t ms = ballot64(is_short), ml = ballot64(is_long);
+    uint32_t incl = nu;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t y = (uint32_t)__shfl_up((int)incl, off, 64);
+        if (lane >= off) incl += y;
+    }
+    if (lane == 63) {
+        sums[0][w] = (uint32_t)__builtin_popcountll(ms);
+        sums[1][w] = (uint32_t)__builtin_popcountll(ml);
+        sums[2][w] = incl;
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        uint32_t* queue = threadIdx.x == 0 ? &a.counters->n_short_fuse
+                          : threadIdx.x == 1 ? &a.counters->n_long_fuse : &a.counters->n_fuse_units;
+        uint32_t run = 0;
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t c = sums[threadIdx.x][k];
+            sums[threadIdx.x][k] = run;
+            run += c;
+        }
+        bases[threadIdx.x] = run ? atomicAdd(queue, run) : 0u;
+    }
+    __syncthreads();
+    const uint32_t sslot = bases[0] + sums[0][w] + (uint32_t)__builtin_popcountll(ms & lanemask_lt());
+    const uint32_t slot = bases[1] + sums[1][w] + (uint32_t)__builtin_popcountll(ml & lanemask_lt());
+    const uint32_t ub = bases[2] + sums[2][w] + incl - nu;
     if (is_short) a.long_list[a.total + 2 * a.n + sslot] = (uint32_t)g;
     if (!is_long) return;
     a.long_list[a.total + slot] = (uint32_t)g;
