@@ -165,7 +165,7 @@ struct DensifyApplyArgs {
 // means mu + R(q) diag(s) z_j and log-scales log s - ln 1.6, and the activated
 // scales and opacity of every copy.  (Rows that are only copied, quaternions,
 // SH, moments and features, go through k_densify_rows.)
-__global__ __launch_bounds__(TB) void k_densify_apply(DensifyApplyArgs a) {
+__device__ __forceinline__ void densify_apply(const DensifyApplyArgs& a) {
     const int64_t g = (int64_t)blockIdx.x * TB + threadIdx.x;
     if (g >= a.map.n || !a.map.keep[g]) return;
     const uint32_t act = a.map.action[g];
@@ -268,7 +268,14 @@ __device__ __forceinline__ void densify_rows(const RowJob& J, const uint32_t* d0
     }
 }
 
-__global__ __launch_bounds__(TB) void k_densify_rows(RowJobs a) {
+// APPLY: the last row of workgroups computes the children's values (b), in the
+// same launch (a launch of its own cost small scenes 5 us).
+template <bool APPLY>
+__global__ __launch_bounds__(TB) void k_densify_rows(RowJobs a, DensifyApplyArgs b) {
+    if (APPLY && blockIdx.y == gridDim.y - 1) {
+        densify_apply(b);
+        return;
+    }
     __shared__ uint32_t d0[ROW_PARENTS], d1[ROW_PARENTS];
     __shared__ uint8_t how[ROW_PARENTS];              // bit 0 kept, 1 copied, 2 split
     const int64_t g0 = (int64_t)blockIdx.x * ROW_PARENTS;
@@ -424,9 +431,10 @@ RowJob row_job(const void* in, void* out, int64_t row_bytes, int zero_new) {
     const int ub = at % 16 == 0 ? 16 : (at % 4 == 0 ? 4 : 1);
     return RowJob{static_cast<const uint8_t*>(in), static_cast<uint8_t*>(out), row_bytes / ub, ub, zero_new};
 }
-void launch_rows(const RowJobs& r, int jobs, hipStream_t s) {
+template <bool APPLY>
+void launch_rows(const RowJobs& r, int jobs, const DensifyApplyArgs& b, hipStream_t s) {
     const unsigned nb = (unsigned)((r.map.n + ROW_PARENTS - 1) / ROW_PARENTS);
-    if (nb > 0) hipLaunchKernelGGL(k_densify_rows, dim3(nb, jobs), dim3(TB), 0, s, r);
+    if (nb > 0) hipLaunchKernelGGL(k_densify_rows<APPLY>, dim3(nb, jobs + (APPLY ? 1 : 0)), dim3(TB), 0, s, r, b);
 }
 fh_status status_of_launch() { return hipGetLastError() == hipSuccess ? FH_OK : FH_E_HIP; }
 }  // namespace
@@ -529,7 +537,6 @@ fh_status fh_densify_apply(int64_t n, int32_t sh_degree, const void* dws, const 
     a.logit_out = out->logit_opacity;
     a.scales_out = scales_out;
     a.opacity_out = opacity_out;
-    hipLaunchKernelGGL(k_densify_apply, dim3(grid_for(n)), dim3(TB), 0, s, a);
     const int64_t nsh = 4 * 3 * (int64_t)(sh_degree + 1) * (sh_degree + 1);
     RowJobs r;
     r.map = map;
@@ -545,7 +552,7 @@ fh_status fh_densify_apply(int64_t n, int32_t sh_degree, const void* dws, const 
         r.job[k++] = row_job(mi[c]->logit_opacity, mo[c]->logit_opacity, 4, 1);
         r.job[k++] = row_job(mi[c]->sh, mo[c]->sh, nsh, 1);
     }
-    launch_rows(r, k, s);
+    launch_rows<true>(r, k, a, s);
     return status_of_launch();
 }
 
@@ -560,7 +567,7 @@ fh_status fh_densify_copy_rows(int64_t n, const void* dws, const void* in, void*
     RowJobs r;
     r.map = DensifyMap{n, n_keep, w.action, w.keep_off, w.extra_off, w.keep};
     r.job[0] = row_job(in, out, row_bytes, 0);
-    launch_rows(r, 1, s);
+    launch_rows<false>(r, 1, DensifyApplyArgs{}, s);
     return status_of_launch();
 }
 
