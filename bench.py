@@ -117,7 +117,7 @@ COPY_BYTES = 1 << 30       # the calibration kernel reads and writes this many b
 
 
 def _short_name(kname: str) -> str:
-    n = kname.split("(")[0]
+    n = kname.replace("(anonymous namespace)::", "").split("(")[0]
     n = n.replace("void ", "").strip()
     return n.split("::")[-1]
 

@@ -159,9 +159,11 @@ typedef struct {
  *   fwd_rows   pixel rows per forward workgroup (BF16 form: 16, 8 for two
  *              workgroups per tile with twice the registers each, or 4 for
  *              four workgroups per tile, several resident per CU, each with
- *              its own barriers; the FP32 VALU forward: 16).
+ *              its own barriers; slices of up to 96 channels at 16 and of 256 at
+ *              8, BF16 features, run as groups of four rows too; the sequential
+ *              FP32 forward: 16).
  *   bwd_chunk  16 or 32 (32 needs d <= 512); kept for callers that set it: the
- *              adjoint of either form walks 32 positions at a time whatever it
+ *              adjoint of either form walks 16 positions at a time whatever it
  *              says.
  *   schedule   order in which the MFMA walk kernels take the (view, tile)
  *              work items: 0 tile index order; 1 longest first (tiles sorted

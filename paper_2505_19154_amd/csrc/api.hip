@@ -151,7 +151,7 @@ static fh_tuning default_tuning(int d, int form, int feat_dtype, int prim) {
                 t.fwd_slice = d;
             } else {
                 t.fwd_slice = d % 256 == 0 ? 256 : 128;
-                t.fwd_rows = d % 256 == 0 && form == FH_FORM_BF16 ? 4 : 8;
+                t.fwd_rows = 8;
             }
         } else {
             t.fwd_slice = d <= 8 ? 8 : (d <= 16 ? 16 : (d <= 32 ? 32 : 64));
