@@ -565,8 +565,9 @@ static void launch_bwd(const fh_plan* p, void* ws, const BwdArgs& a0, const View
 // Rank, Gaussian and record of every visited instance, in visit order.  For
 // calls that sort them by rank next (VISITS_SORT) the launch also clears the
 // segments and the view bits, of which the words of the depth sort's scratch
-// are the store (free once the order stands).
-enum { VISITS_LIST = 0, VISITS_SORT = 1 };
+// are the store (free once the order stands), for gradients (VISITS_GRAD) the
+// rows of the screen-space adjoints too.
+enum { VISITS_LIST = 0, VISITS_SORT = 1, VISITS_GRAD = 2 };
 static void visit_stage(const fh_plan* p, void* ws, int want, hipStream_t s) {
     VisitStageArgs a;
     a.ranges = cbuf<uint32_t>(p, ws, WS_RANGES);
@@ -583,11 +584,14 @@ static void visit_stage(const fh_plan* p, void* ws, int want, hipStream_t s) {
     a.vgid = buf<uint32_t>(p, ws, WS_VGID);
     a.vrec = buf<float4>(p, ws, WS_VREC);
     a.rw = rec_w(p);
-    a.vseg = want == VISITS_SORT ? buf<uint32_t>(p, ws, WS_VSEG) : nullptr;
+    a.vseg = want != VISITS_LIST ? buf<uint32_t>(p, ws, WS_VSEG) : nullptr;
     a.n_vseg = (int64_t)p->n * p->n_views * 2;
-    a.visited = want == VISITS_SORT ? buf<uint32_t>(p, ws, WS_ORDER_TMP) : nullptr;
+    a.visited = want != VISITS_LIST ? buf<uint32_t>(p, ws, WS_ORDER_TMP) : nullptr;
     a.n = p->n;
-    launch_visit_stage(a, (int)p->n_tiles, s);
+    a.grad2d = want == VISITS_GRAD ? buf<float4>(p, ws, WS_GRAD2D) : nullptr;
+    a.n_grad2d = (int64_t)p->n * p->n_views * geom_w(p) / 4;
+    a.n_tiles = (int)p->n_tiles;
+    launch_visit_stage(a, s);
 }
 
 // Visited instances sorted stably by rank (the keys visit_stage wrote): each
@@ -677,7 +681,7 @@ fh_status fh_render_bwd(const fh_plan* p, const fh_gaussians* g, void* ws, const
     a.target_bf16 = target_dtype == FH_BF16;
     const ViewTable vt = view_table(*p);
     prof_begin(FH_K_RENDER_BWD, s);
-    visit_stage(p, ws, VISITS_SORT, s);
+    visit_stage(p, ws, VISITS_GRAD, s);
     launch_bwd(p, ws, a, vt, fuse, s);
     prof_end(FH_K_RENDER_BWD, s);
     if (ndfd) {

@@ -150,6 +150,9 @@ struct VisitStageArgs {
     int64_t n_vseg;
     uint32_t* visited;         // nullable: cleared (n words)
     int64_t n;
+    float4* grad2d;            // nullable: cleared after no overflow (n_grad2d float4)
+    int64_t n_grad2d;
+    int n_tiles;
 };
 struct ReduceArgs {
     const uint32_t* order;
@@ -183,7 +186,7 @@ void launch_render_grad(const BwdArgs& a, const ViewTable& vt, int n_tiles, bool
 // render_fuse.hip: the fusion partials (needs the target); ws: also the weight
 // sums, which the gradient kernel of the same call writes otherwise
 void launch_render_fuse(const BwdArgs& a, const ViewTable& vt, int n_tiles, bool bf16, bool ws, hipStream_t s);
-void launch_visit_stage(const VisitStageArgs& a, int n_tiles, hipStream_t s);
+void launch_visit_stage(const VisitStageArgs& a, hipStream_t s);
 void launch_vseg(const uint32_t* skeys, const Counters* c, int64_t cap, uint32_t* vseg, const uint32_t* order, int64_t n,
                  uint32_t* visited, hipStream_t s);
 // gp: floats per partial row, 12 (Gaussians: 10 used) or 16 (surfels: 14 used)

@@ -12,6 +12,8 @@
 // summed by a wavefront with compensation, and the units are combined in
 // order.  So one long segment does not serialise the launch, and every sum
 // has a fixed order: the results are bitwise reproducible.
+#include <algorithm>
+
 #include "kernels.hpp"
 
 namespace fh {
@@ -44,7 +46,10 @@ __global__ __launch_bounds__(256) void k_visit_stage(VisitStageArgs a) {
     if (a.visited)
         for (int64_t i = i0; i < a.n; i += stride) a.visited[i] = 0u;
     if (a.counters->inst_overflow || a.counters->visit_overflow) return;
+    if (a.grad2d)
+        for (int64_t i = i0; i < a.n_grad2d; i += stride) a.grad2d[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     const int t = blockIdx.x;
+    if (t >= a.n_tiles) return;                                          // (a workgroup that only clears)
     const uint32_t nt = a.tile_niter[t];
     const uint32_t s = a.ranges[2 * t], vo = a.tile_voff[t];
     for (uint32_t pos = threadIdx.x; pos < nt; pos += 256) {
@@ -148,7 +153,10 @@ __global__ __launch_bounds__(256) void k_reduce_geom(ReduceArgs a) {
     const uint32_t b0 = valid ? a.vseg[2 * j] : 0u, b1 = valid ? a.vseg[2 * j + 1] : 0u;
     const bool is_long = b1 - b0 > LONG_GEOM;
     const uint32_t slot = wave_slot(&a.counters->n_long_geom, is_long);
-    if (!valid) return;
+    // (a rank that no walk reached keeps the zero row that the visit staging cleared
+    // in order: written here, through the depth order, the rows of 16M ranks took
+    // 0.46 of this launch's 0.56 ms; there they add 0.20 to 0.34, 3.9 TB/s)
+    if (!valid || b1 == b0) return;
     const int64_t v = j / a.n;
     const uint32_t g = a.order[j];
     if (is_long) {
@@ -467,8 +475,11 @@ int64_t fuse_unit_capacity(int64_t visit_capacity) {
     return visit_capacity * 3 / 64 + 1;
 }
 
-void launch_visit_stage(const VisitStageArgs& a, int n_tiles, hipStream_t s) {
-    hipLaunchKernelGGL(k_visit_stage, dim3(n_tiles), dim3(256), 0, s, a);
+void launch_visit_stage(const VisitStageArgs& a, hipStream_t s) {
+    // (images of few tiles under many Gaussians: workgroups beyond the tiles help to
+    // clear, one for every 4096 float4 of the rows, at most four a CU)
+    const int64_t extra = a.grad2d ? std::min<int64_t>(a.n_grad2d / 4096, 1024) : 0;
+    hipLaunchKernelGGL(k_visit_stage, dim3((unsigned)std::max<int64_t>(a.n_tiles, extra)), dim3(256), 0, s, a);
 }
 
 void launch_vseg(const uint32_t* skeys, const Counters* c, int64_t cap, uint32_t* vseg, const uint32_t* order, int64_t n,
