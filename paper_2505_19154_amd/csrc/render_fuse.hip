@@ -2,7 +2,7 @@
 // tile's pixels (gfx950), both arithmetic forms.
 //
 // Per tile, back to front over the visited list in chunks of 16 positions: one
-// workgroup of four waves, each walking its own 64 pixels, one per lane (w =
+// workgroup, four waves of which walk 64 pixels each, one per lane (w =
 // alpha T, T recovered by division as in the gradient kernel; the chunk's
 // records, one position per lane, reach the walk as DPP row broadcasts).  W^T
 // goes to LDS (double-buffered, one barrier a chunk) and the waves contract it
@@ -85,11 +85,16 @@ __device__ __forceinline__ float row_sum(float v) {
     return add_dpp<0x140>(v);      // row_mirror
 }
 
-// NB: 16-channel blocks per wave (64 NB channels a workgroup, blockIdx.y slices).
-template <int TERMS, int NB, bool WS, bool SURF>
-__global__ __launch_bounds__(256, NB == 4 ? 2 : 3) void k_fuse(BwdArgs a, ViewTable vt, int vec) {
+// NB: 16-channel blocks per wave (16 NB WAVES channels a workgroup, blockIdx.y
+// slices).  WAVES = 8, above 128 channels: the first four waves walk, all eight
+// contract 32 channels each.  With four waves of 64 channels the target alone
+// held 128 registers a lane, two waves a SIMD; the barriers at the chunk ends
+// and the MFMA chains showed: 500k Gaussians at 1920x1080, D = 256, three terms
+// 0.78 -> 0.70 ms, two terms 0.71 -> 0.69.  Up to 128 channels four waves fit.
+template <int TERMS, int NB, int WAVES, bool WS, bool SURF>
+__global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 4 : 3) void k_fuse(BwdArgs a, ViewTable vt, int vec) {
     using RecT = typename PrimRec<SURF>::T;
-    constexpr int DS = 64 * NB;                       // channels of this workgroup
+    constexpr int DS = 16 * NB * WAVES;               // channels of this workgroup
     constexpr int TST = DS + 16;                      // staged target row stride (an odd multiple of 32 bytes)
     constexpr int WEL = 2 * TERMS * CK * PP, TEL = 2 * 32 * TST;
     // W^T [2 buffers][terms][CK][PP]; before the walk, two slabs of 32 target pixels
@@ -109,7 +114,8 @@ __global__ __launch_bounds__(256, NB == 4 ? 2 : 3) void k_fuse(BwdArgs a, ViewTa
     const int d0 = (int)blockIdx.y * DS;
     const int px = tx * TILE + xi, prow = 4 * w + q, py = ty * TILE + prow;
     const float x = (float)px + 0.5f, y = (float)py + 0.5f;
-    const bool inside = px < W && py < H;
+    const bool walks = WAVES == 4 || w < 4;           // (the waves that hold the tile's pixels)
+    const bool inside = walks && px < W && py < H;
     const int64_t p = vt.pix_off[v] + (int64_t)(inside ? py : 0) * W + (inside ? px : 0);
     const int nit = inside ? (int)a.n_iter[p] : 0;
     float T = inside ? a.T_final[p] : 1.0f;
@@ -121,13 +127,13 @@ __global__ __launch_bounds__(256, NB == 4 ? 2 : 3) void k_fuse(BwdArgs a, ViewTa
     // row q, elements m: pixels 32 s + 4 q + m and (m >= 4) 32 s + 16 + 4 q + m - 4
     bf16x8 tg[NB][8];
     {
-        constexpr int IT = 32 * (DS / 8) / 256;       // 8-channel items per thread and slab
+        constexpr int IT = 32 * (DS / 8) / (64 * WAVES);   // 8-channel items per thread and slab
         uint4 raw[IT];
         const uint16_t* src = static_cast<const uint16_t*>(a.target);
         auto load = [&](int s) {
 #pragma unroll
             for (int it = 0; it < IT; ++it) {
-                const int idx = (int)threadIdx.x + 256 * it, k = idx / (DS / 8), c = d0 + 8 * (idx % (DS / 8));
+                const int idx = (int)threadIdx.x + 64 * WAVES * it, k = idx / (DS / 8), c = d0 + 8 * (idx % (DS / 8));
                 const int qy = ty * TILE + 2 * s + (k >> 4), qx = tx * TILE + (k & 15);
                 raw[it] = make_uint4(0u, 0u, 0u, 0u);
                 if (qy < H && qx < W) {
@@ -149,7 +155,7 @@ __global__ __launch_bounds__(256, NB == 4 ? 2 : 3) void k_fuse(BwdArgs a, ViewTa
             uint16_t* st = smem + (s & 1) * 32 * TST;
 #pragma unroll
             for (int it = 0; it < IT; ++it) {
-                const int idx = (int)threadIdx.x + 256 * it, k = idx / (DS / 8), c = 8 * (idx % (DS / 8));
+                const int idx = (int)threadIdx.x + 64 * WAVES * it, k = idx / (DS / 8), c = 8 * (idx % (DS / 8));
                 *reinterpret_cast<uint4*>(st + k * TST + c) = raw[it];
             }
             if (s < 7) load(s + 1);
@@ -176,7 +182,7 @@ __global__ __launch_bounds__(256, NB == 4 ? 2 : 3) void k_fuse(BwdArgs a, ViewTa
         const RecT rn = load_rec<SURF>(a.vrec, at(ncs));
         uint16_t* sw = smem + buf * TERMS * CK * PP;
         const int rem = nit - cs < cnt ? nit - cs : cnt;
-        unroll_seq(std::make_integer_sequence<int, CK>{}, [&](auto kc) {
+        if (walks) unroll_seq(std::make_integer_sequence<int, CK>{}, [&](auto kc) {
             constexpr int k = CK - 1 - decltype(kc)::value;
             const float alpha = prim_alpha<SURF>(bcast_rec<k>(rc), x, y);
             const float al = (alpha >= ALPHA_MIN && k < rem) ? alpha : 0.0f;
@@ -434,22 +440,23 @@ __global__ __launch_bounds__(1024) void k_fuse_f32(BwdArgs a, ViewTable vt) {
 }
 
 // ---------------------------------------------------------------------------
-template <int TERMS, int NB, bool SURF>
+template <int TERMS, int NB, int WAVES, bool SURF>
 void launch_nb(const BwdArgs& a, const ViewTable& vt, int n_tiles, bool ws, hipStream_t s) {
     // 16-byte target loads where every row is aligned to them
     const int vec = a.d % 8 == 0 && reinterpret_cast<uintptr_t>(a.target) % 16 == 0;
-    const dim3 grid(n_tiles, (a.d + 64 * NB - 1) / (64 * NB));
+    constexpr int DS = 16 * NB * WAVES;
+    const dim3 grid(n_tiles, (a.d + DS - 1) / DS), block(64 * WAVES);
     if (ws)
-        hipLaunchKernelGGL((k_fuse<TERMS, NB, true, SURF>), grid, dim3(256), 0, s, a, vt, vec);
+        hipLaunchKernelGGL((k_fuse<TERMS, NB, WAVES, true, SURF>), grid, block, 0, s, a, vt, vec);
     else
-        hipLaunchKernelGGL((k_fuse<TERMS, NB, false, SURF>), grid, dim3(256), 0, s, a, vt, vec);
+        hipLaunchKernelGGL((k_fuse<TERMS, NB, WAVES, false, SURF>), grid, block, 0, s, a, vt, vec);
 }
 
 template <int TERMS, bool SURF>
 void launch_terms(const BwdArgs& a, const ViewTable& vt, int n_tiles, bool ws, hipStream_t s) {
-    if (a.d <= 64) launch_nb<TERMS, 1, SURF>(a, vt, n_tiles, ws, s);
-    else if (a.d <= 128) launch_nb<TERMS, 2, SURF>(a, vt, n_tiles, ws, s);
-    else launch_nb<TERMS, 4, SURF>(a, vt, n_tiles, ws, s);
+    if (a.d <= 64) launch_nb<TERMS, 1, 4, SURF>(a, vt, n_tiles, ws, s);
+    else if (a.d <= 128) launch_nb<TERMS, 2, 4, SURF>(a, vt, n_tiles, ws, s);
+    else launch_nb<TERMS, 2, 8, SURF>(a, vt, n_tiles, ws, s);
 }
 
 template <int NB, bool SURF>
