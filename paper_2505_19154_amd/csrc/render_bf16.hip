@@ -98,7 +98,7 @@ __global__ __launch_bounds__(64 * ROWS, (ROWS <= 8 && DS <= 128 && !FS) ? 4 : (R
     constexpr int NFR = FS ? 2 * NIT : NIT;               // 16-byte registers of one chunk's feature items
     constexpr int FROW = 2 * DS + 32, FT = FK * FROW;     // bytes of a position's row, and of a feature tile
     __shared__ __attribute__((aligned(16))) unsigned char sft[2][NFT * FT];
-    __shared__ uint32_t smax[ROWS];
+    __shared__ uint32_t smax[ROWS], sodd;
     __shared__ __attribute__((aligned(16))) uint8_t sbusy[2][16];   // per wave: a pixel still walking
     if (a.counters->inst_overflow) return;
     constexpr int NG = TILE / ROWS;                      // row groups per tile
@@ -126,7 +126,17 @@ __global__ __launch_bounds__(64 * ROWS, (ROWS <= 8 && DS <= 128 && !FS) ? 4 : (R
     auto put_rec = [&](int buf, uint32_t pos, const RecT& r, uint32_t g) {
         const bool real = pos < len;
         // padding: opacity 0 never blends
-        const RecT o = real ? r : pad_rec<SURF>();
+        RecT o = real ? r : pad_rec<SURF>();
+        // (an infinite colour enters the branch-free sums as zero, 0 * inf must not
+        // reach the pixels that do not blend it, and is added at the end; the
+        // projection leaves no NaN and nothing negative)
+        const float INF = __builtin_inff();
+        if (fmaxf(fmaxf(o.r2.y, o.r2.z), o.r2.w) == INF) {
+            sodd = 1u;
+            o.r2.y = o.r2.y == INF ? 0.0f : o.r2.y;
+            o.r2.z = o.r2.z == INF ? 0.0f : o.r2.z;
+            o.r2.w = o.r2.w == INF ? 0.0f : o.r2.w;
+        }
         lds_put_prec<SURF, RG>(srec4[buf], k, o);
         sg[buf][k] = real ? g : 0u;
     };
@@ -197,6 +207,7 @@ __global__ __launch_bounds__(64 * ROWS, (ROWS <= 8 && DS <= 128 && !FS) ? 4 : (R
 
     // prologue: chunks 0 and 1 into LDS, chunk 2's ranks into registers, then chunk 0's features
     uint32_t rk2 = 0u;
+    if (threadIdx.x == 0) sodd = 0u;   // (set by the same wave)
     if (k < FK && len > 0) {
         const uint32_t j0 = list_load(list_rs, (uint32_t)k);
         const uint32_t j1 = list_load(list_rs, (uint32_t)(FK + k));
@@ -363,14 +374,6 @@ __global__ __launch_bounds__(64 * ROWS, (ROWS <= 8 && DS <= 128 && !FS) ? 4 : (R
     c2 += __shfl_xor(c2, 16, 64);
     c2 += __shfl_xor(c2, 32, 64);
     const int64_t rowp = vt.pix_off[v] + (int64_t)py * vt.width[v];
-    if (slice == 0 && q == 0 && inside) {
-        const int64_t p = rowp + px;
-        a.C[3 * p] = c0;
-        a.C[3 * p + 1] = c1;
-        a.C[3 * p + 2] = c2;
-        a.T[p] = T;
-        a.n_iter[p] = last;
-    }
     // F: lane holds F[pixel 4q + r of this row][channel 16 j + xi]
     if (py < vt.height[v]) {
 #pragma unroll
@@ -382,6 +385,23 @@ __global__ __launch_bounds__(64 * ROWS, (ROWS <= 8 && DS <= 128 && !FS) ? 4 : (R
                 for (int j = 0; j < NB; ++j) fo[16 * j] = acc[j][r];
             }
         }
+    }
+    if (slice == 0 && q == 0 && inside) {
+        if (sodd != 0u) {   // (rare: infinite colours, by a second walk; up to the last blend every alpha of 1/255 blends)
+            for (uint32_t pos = 0; pos < last; ++pos) {
+                const RecT r = load_rec<SURF>(a.rrec, list[s + pos] & rmask);
+                if (prim_alpha<SURF>(r, x, y) < ALPHA_MIN) continue;
+                c0 = r.r2.y == __builtin_inff() ? r.r2.y : c0;
+                c1 = r.r2.z == __builtin_inff() ? r.r2.z : c1;
+                c2 = r.r2.w == __builtin_inff() ? r.r2.w : c2;
+            }
+        }
+        const int64_t p = rowp + px;
+        a.C[3 * p] = c0;
+        a.C[3 * p + 1] = c1;
+        a.C[3 * p + 2] = c2;
+        a.T[p] = T;
+        a.n_iter[p] = last;
     }
     if (slice == 0) {
         // the tile's traversal length: max over its row groups (tile_niter is
