@@ -313,6 +313,14 @@ __global__ __launch_bounds__(64 * ROWS, (ROWS <= 8 && DS <= 128 && !FS) ? 4 : (R
         if (!done) {
             T = fabsf(Tr.r0 < 0.0f ? Tr.r0 : (Tr.r1 < 0.0f ? Tr.r1 : (Tr.r2 < 0.0f ? Tr.r2 : Tr.r3)));
             done = fminf(fminf(Tr.r0, Tr.r1), fminf(Tr.r2, Tr.r3)) < 0.0f;
+            // A lane starts from T times the product of the lanes before it, which
+            // may round below T_MIN where the lane before ended at or above it by its
+            // own sequence of products.  Then no lane carries the stop's sign: the
+            // pixel stopped there, with the T of the last open lane.
+            if (T < T_MIN) {
+                T = Tr.r2 >= T_MIN ? Tr.r2 : (Tr.r1 >= T_MIN ? Tr.r1 : Tr.r0);
+                done = true;
+            }
         }
         const Rows4 Lr = rows4(__uint_as_float(mylast));
         const uint32_t lm = max(max(__float_as_uint(Lr.r0), __float_as_uint(Lr.r1)),
