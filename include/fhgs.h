@@ -416,9 +416,11 @@ fh_status fh_render_fwd_static(const fh_plan *plan, const fh_gaussians *g, const
 fh_status fh_tuning_candidates(const fh_plan *plan, int32_t which, fh_tuning *out, int32_t max, int32_t *count);
 
 /* Autotuner (the batched form picks its launch shape on the real workload):
- * times every candidate of fh_tuning_candidates for FH_K_RENDER_FWD, then for
+ * times the candidates of fh_tuning_candidates for FH_K_RENDER_FWD, then for
  * FH_K_RENDER_BWD, `reps` calls each after one warm-up, with HIP events on
- * `stream`, and writes the fastest into plan->tuning.  Needs the state of a
+ * `stream`, and writes the fastest into plan->tuning.  Candidates that start the
+ * same kernels are timed once, and plan->tuning stays as it is where it already
+ * starts the fastest.  Needs the state of a
  * completed fh_project + fh_bin_sort + fh_render_fwd in ws with no capacity
  * overflow.  fwd, grads and acc are written as by the calls they time (acc is
  * accumulated into: pass a scratch accumulator, or NULL to time without

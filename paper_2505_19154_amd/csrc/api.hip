@@ -178,6 +178,16 @@ static bool tuning_ok(const fh_plan* p) {
            bwd_chunk_ok(p->d, p->tuning.bwd_chunk) && (p->tuning.schedule == 0 || p->tuning.schedule == 1);
 }
 
+// Whether two launch shapes of a plan start the same kernels: the adjoint of the
+// FP32 form and the sequential forward have one shape whatever the fields say, and
+// (256 channels, 8 rows) of BF16 features runs as (256, 4) (see launch_fwd_mfma).
+static bool same_launch(const fh_plan* p, int which, const fh_tuning& a, const fh_tuning& b) {
+    if (which == FH_K_RENDER_BWD) return p->form == FH_FORM_F32 || a.schedule == b.schedule;
+    if (!mfma_forward(p->d, p->form, p->feat_dtype, p->primitive)) return true;
+    auto rows = [&](const fh_tuning& t) { return p->feat_dtype == FH_BF16 && t.fwd_slice == 256 ? 4 : t.fwd_rows; };
+    return a.schedule == b.schedule && a.fwd_slice == b.fwd_slice && rows(a) == rows(b);
+}
+
 // The work order of the MFMA walk kernels (fh_tuning.schedule): nullptr for
 // tile index order; else the tiles sorted by cost, longest first (a stable
 // sort of 16-bit keys, ties in index order), cost = the list length
@@ -852,6 +862,10 @@ fh_status fh_autotune(fh_plan* p, const fh_gaussians* g, void* ws, const fh_imag
         int best = -1;
         float best_ms = 0.0f;
         for (int c = 0; c < nc; ++c) {
+            // one timing a distinct launch: between equal ones noise would pick
+            bool timed = false;
+            for (int e = 0; e < c; ++e) timed = timed || same_launch(p, which, cand[e], cand[c]);
+            if (timed) continue;
             fh_plan q = *p;
             q.tuning = cand[c];
             float ms = 0.0f;
@@ -866,7 +880,8 @@ fh_status fh_autotune(fh_plan* p, const fh_gaussians* g, void* ws, const fh_imag
                 best_ms = ms;
             }
         }
-        p->tuning = cand[best];
+        // (the plan's own fields stay where they already start the fastest launch)
+        if (!same_launch(p, which, cand[best], p->tuning)) p->tuning = cand[best];
     }
     return FH_OK;
 }
