@@ -73,7 +73,8 @@ __global__ __launch_bounds__(256, 2) void k_render_fwd_f32(RenderArgs a, ViewTab
     __shared__ __attribute__((aligned(16))) float sft[NB > 0 ? (FB ? 2 * FK * FROW / 4 : 2 * FK * FST) : 4];
     __shared__ float sw[NB > 0 ? 4 * WROWS * WST : 4];
     __shared__ uint32_t smax[4], sodd;
-    __shared__ uint8_t sbusy[2][4];
+    __shared__ __attribute__((aligned(4))) uint8_t sbusy[2][4];   // per wave: a pixel still walking (read as one word)
+    static_assert(__alignof__(sbusy) >= 4, "the four flags are read as one word");
     if (a.counters->inst_overflow) return;
     const int t = blockIdx.x, slice = blockIdx.y, d0 = slice * DS;
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
