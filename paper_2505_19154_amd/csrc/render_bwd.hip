@@ -442,12 +442,11 @@ __global__ __launch_bounds__(256, min_waves(BF16, NS, SURF)) void k_bwd(BwdArgs 
         //      sum dp (q1 a e_y + q2 b e_x) = B Sx + C dy S0,
         //    A = q1 e_x^2 + q2 e_y^2, B = (q1 - q2) e_x e_y, C = q1 e_y^2 + q2 e_x^2,
         //    S0 = sum dp, Sx = sum dp dx, Sxx = sum dp dx^2.  For a long thin splat
-        //    A Sx and B dy S0 nearly cancel (q2 dwarfs q1, and the part of q2 is b,
-        //    small beside dx and dy), so the FP32 form sums a and b themselves, Sa and
-        //    Sb, and combines q1 e_x Sa - q2 e_y Sb and q1 e_y Sa + q2 e_x Sb: four
-        //    instructions more a pixel and position (0.5 to 0.8 % of a step); axes of 60
-        //    and 1.5 pixels: error of dL/d(u, v) over the terms' sizes 1.0e-7 -> 1.1e-8,
-        //    of terms formed pixel by pixel 0.9e-8.  A surfel's nine
+        //    A Sx and B dy S0 nearly cancel (q1, of the short axis, dwarfs q2, and its part
+        //    is a, small beside dx and dy), so the FP32 form sums a itself, Sa, and combines
+        //    q1 e_x Sa - q2 e_y Sb and q1 e_y Sa + q2 e_x Sb, Sb = e_x dy S0 - e_y Sx: two instructions more a pixel and position
+        //    (0.4 % of a step); axes of 60 and 1.5 pixels: error of dL/d(u, v) over the
+        //    terms' sizes 1.0e-7 -> 1.0e-8, of terms formed pixel by pixel 0.9e-8.  A surfel's nine
         //    record terms are linear in dL/dk = dp (-u/k2, -v/k2, (u^2 + v^2)/k2)
         //    = (l0, l1, l2) with coefficients from the record and (dx, dy):
         //      dx_c: -b1 L0 + b0 L1 + e2 L2,  dy_c: a1 L0 - a0 L1 + e1 L2,
@@ -465,8 +464,8 @@ __global__ __launch_bounds__(256, min_waves(BF16, NS, SURF)) void k_bwd(BwdArgs 
             const float dy = (y - rc.r0.y) - rc.r0.w;
             float x0 = (float)(tx * TILE) + 0.5f;
             asm volatile("" : "+v"(x0));   // (x0 + m is formed here: not sixteen registers held across the chunks)
-            float s0 = 0.0f, sx = 0.0f, sxx = 0.0f, sa = 0.0f, sb = 0.0f;
-            const float exdy = rc.r1.x * dy, eydy = rc.r1.y * dy;   // (Gaussians)
+            float s0 = 0.0f, sx = 0.0f, sxx = 0.0f, sa = 0.0f;
+            const float eydy = rc.r1.y * dy;   // (Gaussians)
             float L0 = 0.0f, L1 = 0.0f, L2 = 0.0f, L0x = 0.0f, L1x = 0.0f, L2x = 0.0f;
 #pragma unroll
             for (int m = 0; m < TILE; ++m) {
@@ -488,10 +487,7 @@ __global__ __launch_bounds__(256, min_waves(BF16, NS, SURF)) void k_bwd(BwdArgs 
                     L1x = __builtin_fmaf(l1, dx, L1x);
                     L2x = __builtin_fmaf(l2, dx, L2x);
                 } else {
-                    if constexpr (!BF16) {
-                        sa = __builtin_fmaf(e.y, __builtin_fmaf(rc.r1.x, dx, eydy), sa);
-                        sb = __builtin_fmaf(e.y, __builtin_fmaf(-rc.r1.y, dx, exdy), sb);
-                    }
+                    if constexpr (!BF16) sa = __builtin_fmaf(e.y, __builtin_fmaf(rc.r1.x, dx, eydy), sa);
                     const float pdx = e.y * dx;
                     sx += pdx;
                     sxx = __builtin_fmaf(pdx, dx, sxx);
@@ -517,6 +513,7 @@ __global__ __launch_bounds__(256, min_waves(BF16, NS, SURF)) void k_bwd(BwdArgs 
                     qv[0] = -2.0f * LN2 * (A * sx + B * sy);
                     qv[1] = -2.0f * LN2 * (B * sx + C * sy);
                 } else {
+                    const float sb = __builtin_fmaf(ex, sy, -(ey * sx));
                     qv[0] = -2.0f * LN2 * (q1 * ex * sa - q2 * ey * sb);
                     qv[1] = -2.0f * LN2 * (q1 * ey * sa + q2 * ex * sb);
                 }
