@@ -678,12 +678,12 @@ __global__ __launch_bounds__(512, TERMS == 2 && VEC ? 4 : 2) void k_dot(BwdArgs 
                 float rest = vals[m];
 #pragma unroll
                 for (int c = 0; c < TERMS; ++c) {
-                    // (the first term stays finite: values above the largest BF16 would round
-                    // to an infinity; an infinity or NaN is its second term)
+                    // (all terms but the last stay finite: values above the largest BF16 would
+                    // round to an infinity; an infinity or NaN is the last term)
                     const float top = 3.38953139e38f;
-                    const __bf16 b = (__bf16)(c == 0 ? __builtin_amdgcn_fmed3f(rest, -top, top) : rest);
+                    const __bf16 b = (__bf16)(c < TERMS - 1 ? __builtin_amdgcn_fmed3f(rest, -top, top) : rest);
                     d[c][s][m] = b;
-                    rest = c == 0 || isfinite((float)b) ? rest - (float)b : 0.0f;
+                    rest -= (float)b;
                 }
             }
         }
