@@ -551,6 +551,7 @@ static void fill_bwd_args(const fh_plan* p, const fh_gaussians* g, void* ws, con
     a.part_fuse = buf<float>(p, ws, WS_PART_FUSE);
     a.tile_order = nullptr;
     a.g = nullptr;
+    a.tseg = nullptr;
     a.d0 = 0;
     a.prim = p->primitive;
 }
@@ -568,6 +569,12 @@ static void launch_bwd(const fh_plan* p, void* ws, const BwdArgs& a0, const View
     if (bf16) a.tile_order = tile_schedule(p, ws, false, s);
     if (p->d >= 256)
         a.g = bf16 ? buf<float>(p, ws, p->d > 256 ? WS_GREC : WS_WREC) : buf<float>(p, ws, WS_PART_FUSE);
+    // T at the segment ends for the fusion of the same call, lent the unit sums of
+    // its reduction, which are written later
+    const int64_t have = fuse_unit_capacity(p->visit_capacity) * (2 * (int64_t)p->d + 2);
+    if (bf16 && fuse && a.dC != nullptr && list_parts(p->n_tiles) > 1 &&
+        (p->visit_capacity / T_SEG + p->n_tiles) * TILE_PIX <= have)
+        a.tseg = buf<float>(p, ws, WS_UPART);
     if (a.dC != nullptr) launch_render_grad(a, vt, (int)p->n_tiles, bf16, s);
     if (fuse) launch_render_fuse(a, vt, (int)p->n_tiles, bf16, a.dC == nullptr, s);
 }

@@ -130,8 +130,13 @@ struct BwdArgs {
     // (from channel d0) and read by the walk
     float* g;
     int d0;
+    // nullable: T of every pixel at the segment ends of its tile's list, counted
+    // from the list's end ([voff / T_SEG + tile + segment - 1][256]), left by the walk
+    // of the gradients for the fusion of the same call
+    float* tseg;
     int prim;                     // fh_primitive
 };
+constexpr int T_SEG = 128;        // positions a segment
 struct VisitStageArgs {
     const uint32_t* ranges;
     const uint32_t* tile_niter;
@@ -183,6 +188,13 @@ void launch_render_fwd_bf16(const RenderArgs& a, const ViewTable& vt, int n_tile
 // render_bwd.hip: the gradient kernel (needs dC); bf16: the BF16 form.  With dF
 // and d >= 256 it needs a.g
 void launch_render_grad(const BwdArgs& a, const ViewTable& vt, int n_tiles, bool bf16, hipStream_t s);
+// Workgroups that share a tile's list where the list can be cut (the fusion with
+// a.tseg, f . dF): with one a tile images of few tiles leave the chip idle, each a
+// chain of a few hundred cycles a position.  About 1024 in all, four a CU.  Steps with
+// fusion, 4,000 Gaussians, 128 channels: 12 tiles 926 -> 696 us, 48 tiles 538 -> 440,
+// 320 tiles 372 -> 344, 432 tiles 373 -> 355; 100,000 of 256 channels 432 tiles 595 ->
+// 589, 512 tiles 592 -> 602.
+inline int list_parts(int64_t n_tiles) { return n_tiles <= 448 ? (int)(n_tiles <= 64 ? 16 : 1024 / n_tiles) : 1; }
 // render_fuse.hip: the fusion partials (needs the target); ws: also the weight
 // sums, which the gradient kernel of the same call writes otherwise
 void launch_render_fuse(const BwdArgs& a, const ViewTable& vt, int n_tiles, bool bf16, bool ws, hipStream_t s);

@@ -38,6 +38,7 @@
 //
 // SURF: the surfel primitive (Section 3.1): four-float4 records, the density at
 // the ray-plane intersection, 14 terms per instance in rows of 16 floats.
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -246,7 +247,8 @@ constexpr int min_waves(bool bf16, int ns, bool surf) {
 
 // MODE: G_WHOLE the whole width at once; G_CARRY the feature part of g read
 // from a.g (k_dot wrote it; NS = 0).
-template <bool BF16, int NS, bool FB, bool SURF, int MODE>
+// SEG: T at the segment ends goes to a.tseg.
+template <bool BF16, int NS, bool FB, bool SURF, int MODE, bool SEG>
 __global__ __launch_bounds__(256, min_waves(BF16, NS, SURF)) void k_bwd(BwdArgs a, ViewTable vt, int vec_f, int vec_df) {
     using RecT = typename PrimRec<SURF>::T;
     using Ops = typename OperandsOf<BF16, FB, NS>::T;
@@ -345,6 +347,9 @@ __global__ __launch_bounds__(256, min_waves(BF16, NS, SURF)) void k_bwd(BwdArgs 
     float2* wd = swd[w];
     for (int ce = nt; ce > 0; ce = cs, cs = start_of(cs), buf ^= 1) {
         const int cnt = ce - cs, ncs = start_of(cs);
+        if constexpr (SEG)   // (thread = pixel of the tile)
+            if (ce < nt && (nt - ce) % T_SEG == 0)
+                a.tseg[(voff / T_SEG + t + (nt - ce) / T_SEG - 1) * TILE_PIX + threadIdx.x] = T;
         // 1. G: lane (q, xi) gets positions 4 q + r of pixel (row 4 w + h, column xi)
         f32x4 gk[4];
         {
@@ -584,7 +589,8 @@ __global__ __launch_bounds__(256, min_waves(BF16, NS, SURF)) void k_bwd(BwdArgs 
 // (three roundings to 8 bits cover 24), so that only the FP32 accumulation
 // rounds.  0: FP32 features, FP32 operands on v_mfma_f32_16x16x4_f32.
 // VEC: 16-byte feature loads, the slice wholly inside the width.
-template <int TERMS, int NS, bool VEC>
+// PARTS: a workgroup takes every gridDim.y-th chunk of the list (images of few tiles).
+template <int TERMS, int NS, bool VEC, bool PARTS>
 __global__ __launch_bounds__(512, TERMS == 2 && VEC ? 4 : 2) void k_dot(BwdArgs a, ViewTable vt, int n_tiles, int vec_df) {
     constexpr int DK = TERMS > 0 ? 128 : 64;                 // positions per chunk
     constexpr int EB = TERMS > 0 ? 2 : 4;                    // bytes per feature element
@@ -597,7 +603,8 @@ __global__ __launch_bounds__(512, TERMS == 2 && VEC ? 4 : 2) void k_dot(BwdArgs 
     const int j = (int)blockIdx.x >> 3, t = (j >> 1) * 8 + ((int)blockIdx.x & 7);
     if (t >= n_tiles) return;
     const int nt = __builtin_amdgcn_readfirstlane((int)a.tile_niter[t]);
-    if (nt == 0) return;
+    const int c0 = PARTS ? (int)blockIdx.y * DK : 0, step = PARTS ? (int)gridDim.y * DK : DK;
+    if (c0 >= nt) return;
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int q = lane >> 4, xi = lane & 15;
     const int v = view_of_tile(vt, t);
@@ -637,12 +644,12 @@ __global__ __launch_bounds__(512, TERMS == 2 && VEC ? 4 : 2) void k_dot(BwdArgs 
         }
     };
     auto run = [&](auto mul) {
-        for (int cs = 0; cs < nt; cs += DK) {
+        for (int cs = c0; cs < nt; cs += step) {
             uint32_t gid[IT];
             u32x4 raw[IT];
             load_gid(cs, gid);
             load(gid, raw);
-            if (cs > 0) __syncthreads();   // (the previous chunk's readers are done)
+            if (cs > c0) __syncthreads();   // (the previous chunk's readers are done)
 #pragma unroll
             for (int it = 0; it < IT; ++it) {
                 const int idx = (int)threadIdx.x + 512 * it;
@@ -728,7 +735,12 @@ void launch(const BwdArgs& a, const ViewTable& vt, int n_tiles, hipStream_t s) {
     // 16-byte (FP32 form with BF16 storage: 8-byte) feature and dF loads where every row is aligned to them
     const int vec_f = a.d % 4 == 0 && reinterpret_cast<uintptr_t>(a.feat) % (FB ? 8 : 16) == 0;
     const int vec_df = a.d % 4 == 0 && reinterpret_cast<uintptr_t>(a.dF) % 16 == 0;
-    hipLaunchKernelGGL((k_bwd<BF16, NS, FB, SURF, MODE>), dim3(n_tiles), dim3(256), 0, s, a, vt, vec_f, vec_df);
+    if constexpr (BF16)
+        if (a.tseg) {
+            hipLaunchKernelGGL((k_bwd<BF16, NS, FB, SURF, MODE, true>), dim3(n_tiles), dim3(256), 0, s, a, vt, vec_f, vec_df);
+            return;
+        }
+    hipLaunchKernelGGL((k_bwd<BF16, NS, FB, SURF, MODE, false>), dim3(n_tiles), dim3(256), 0, s, a, vt, vec_f, vec_df);
 }
 
 // the feature part of g in slices of 256 channels into a.g, then the walk
@@ -737,16 +749,23 @@ void launch_dot(const BwdArgs& a0, const ViewTable& vt, int n_tiles, hipStream_t
     const bool vec_f = a0.d % (TERMS > 0 ? 8 : 4) == 0 && reinterpret_cast<uintptr_t>(a0.feat) % 16 == 0;
     const int vec_df = a0.d % 4 == 0 && reinterpret_cast<uintptr_t>(a0.dF) % 16 == 0;
     BwdArgs a = a0;
-    const dim3 grid((unsigned)(((n_tiles + 7) / 8) * 16));
-    for (a.d0 = 0; a.d0 < a.d;) {
+    const unsigned parts = (unsigned)std::max(list_parts(n_tiles) / 2, 1);   // (two workgroups a tile already)
+    const dim3 grid((unsigned)(((n_tiles + 7) / 8) * 16), parts);
+    auto slice = [&](auto p) {
+        constexpr bool PARTS = decltype(p)::value;
         const int rest = a.d - a.d0;
         if (vec_f && rest >= 256)
-            hipLaunchKernelGGL((k_dot<TERMS, 8, true>), grid, dim3(512), 0, s, a, vt, n_tiles, vec_df);
+            hipLaunchKernelGGL((k_dot<TERMS, 8, true, PARTS>), grid, dim3(512), 0, s, a, vt, n_tiles, vec_df);
         else if (vec_f && rest == 128)
-            hipLaunchKernelGGL((k_dot<TERMS, 4, true>), grid, dim3(512), 0, s, a, vt, n_tiles, vec_df);
+            hipLaunchKernelGGL((k_dot<TERMS, 4, true, PARTS>), grid, dim3(512), 0, s, a, vt, n_tiles, vec_df);
         else
-            hipLaunchKernelGGL((k_dot<TERMS, 8, false>), grid, dim3(512), 0, s, a, vt, n_tiles, vec_df);
-        a.d0 += 256;
+            hipLaunchKernelGGL((k_dot<TERMS, 8, false, PARTS>), grid, dim3(512), 0, s, a, vt, n_tiles, vec_df);
+    };
+    for (a.d0 = 0; a.d0 < a.d; a.d0 += 256) {
+        if (parts > 1)
+            slice(std::true_type{});
+        else
+            slice(std::false_type{});
     }
     launch<TERMS == 2, 0, false, SURF, G_CARRY>(a, vt, n_tiles, s);
 }

@@ -23,7 +23,10 @@
 // the target's one read.  Reading weights recorded by the gradient kernel
 // instead costs 1 KB written and read a visit: 128 channels, 1M Gaussians in 16
 // views 4.14 ms with, 3.36 ms without; 256 channels, 500k at 1920x1080 0.66 and
-// 0.72 ms, but 0.2 ms of recording in the gradient kernel.
+// 0.72 ms, but 0.2 ms of recording in the gradient kernel.  Images of few tiles are
+// bound by the chain of the walk instead (PARTS, BF16 form): the gradient kernel
+// leaves T at every 128th position (8 bytes a visit), and the segments of a list run
+// side by side (lists of 7,900 positions in 16 tiles: 1.00 ms for the whole walk).
 #include <type_traits>
 #include <utility>
 
@@ -91,7 +94,7 @@ __device__ __forceinline__ float row_sum(float v) {
 // held 128 registers a lane, two waves a SIMD; the barriers at the chunk ends
 // and the MFMA chains showed: 500k Gaussians at 1920x1080, D = 256, three terms
 // 0.78 -> 0.70 ms, two terms 0.71 -> 0.69.  Up to 128 channels four waves fit.
-template <int TERMS, int NB, int WAVES, bool WS, bool SURF>
+template <int TERMS, int NB, int WAVES, bool WS, bool SURF, bool PARTS>
 __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 4 : 3) void k_fuse(BwdArgs a, ViewTable vt, int vec) {
     using RecT = typename PrimRec<SURF>::T;
     constexpr int DS = 16 * NB * WAVES;               // channels of this workgroup
@@ -120,7 +123,13 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 4 : 3) void k_fuse(BwdArgs
     const int nit = inside ? (int)a.n_iter[p] : 0;
     float T = inside ? a.T_final[p] : 1.0f;
     auto at = [&](int cs) { return voff + (cs + xi < nt ? cs + xi : nt - 1); };
-    int cs = nt - CK > 0 ? nt - CK : 0;
+    // PARTS: segments blockIdx.z, blockIdx.z + gridDim.z, ... of the list, counted
+    // from its end, each from the T that the gradient walk left there
+    const int len = PARTS ? T_SEG : nt;
+    int end = nt - (PARTS ? (int)blockIdx.z * len : 0);
+    if (PARTS && end <= 0) return;
+    int first = PARTS && end > len ? end - len : 0;
+    int cs = end - CK > first ? end - CK : first;
     RecT rc = load_rec<SURF>(a.vrec, at(cs));
 
     // target operands of this wave's channels d0 + 16 (NB w + j) + xi: slab s, lane
@@ -177,65 +186,75 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 4 : 3) void k_fuse(BwdArgs
     // column of the lane's pixel in a W^T row, in the order of the target operands
     const int col = 32 * (prow >> 1) + 8 * (xi >> 2) + 4 * (prow & 1) + (xi & 3);
     int buf = 0;
-    for (int ce = nt; ce > 0; ce -= CK, buf ^= 1) {
-        const int cnt = ce - cs, ncs = cs - CK > 0 ? cs - CK : 0;
-        const RecT rn = load_rec<SURF>(a.vrec, at(ncs));
-        uint16_t* sw = smem + buf * TERMS * CK * PP;
-        const int rem = nit - cs < cnt ? nit - cs : cnt;
-        if (walks) unroll_seq(std::make_integer_sequence<int, CK>{}, [&](auto kc) {
-            constexpr int k = CK - 1 - decltype(kc)::value;
-            const float alpha = prim_alpha<SURF>(bcast_rec<k>(rc), x, y);
-            const float al = (alpha >= ALPHA_MIN && k < rem) ? alpha : 0.0f;
-            T = T * rcp1(1.0f - al);
-            const float wv = al * T;
-            float rest = wv;
+    for (;;) {
+        if constexpr (PARTS)
+            if (end < nt && inside)
+                T = a.tseg[(voff / T_SEG + t + (nt - end) / T_SEG - 1) * TILE_PIX + prow * TILE + xi];
+        for (int ce = end; ce > first; ce -= CK, buf ^= 1) {
+            const int cnt = ce - cs, ncs = cs - CK > first ? cs - CK : first;
+            const RecT rn = load_rec<SURF>(a.vrec, at(ncs));
+            uint16_t* sw = smem + buf * TERMS * CK * PP;
+            const int rem = nit - cs < cnt ? nit - cs : cnt;
+            if (walks) unroll_seq(std::make_integer_sequence<int, CK>{}, [&](auto kc) {
+                constexpr int k = CK - 1 - decltype(kc)::value;
+                const float alpha = prim_alpha<SURF>(bcast_rec<k>(rc), x, y);
+                const float al = (alpha >= ALPHA_MIN && k < rem) ? alpha : 0.0f;
+                T = T * rcp1(1.0f - al);
+                const float wv = al * T;
+                float rest = wv;
 #pragma unroll
-            for (int c = 0; c < TERMS; ++c) {
-                const __bf16 b = (__bf16)rest;
-                sw[(c * CK + k) * PP + col] = __builtin_bit_cast(uint16_t, b);
-                rest -= (float)b;
+                for (int c = 0; c < TERMS; ++c) {
+                    const __bf16 b = (__bf16)rest;
+                    sw[(c * CK + k) * PP + col] = __builtin_bit_cast(uint16_t, b);
+                    rest -= (float)b;
+                }
+                if constexpr (WS) {
+                    const float rs = row_sum(wv);
+                    if (xi == 0) swsum[buf][k][prow] = rs;
+                }
+            });
+            __syncthreads();
+            if (WS && d0 == 0 && (int)threadIdx.x < cnt) {
+                float ws = 0.0f;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) ws += swsum[buf][threadIdx.x][r];
+                a.part_geom[(voff + cs + threadIdx.x) * PrimRec<SURF>::GP + PrimRec<SURF>::WSLOT] = ws;
             }
-            if constexpr (WS) {
-                const float rs = row_sum(wv);
-                if (xi == 0) swsum[buf][k][prow] = rs;
-            }
-        });
-        __syncthreads();
-        if (WS && d0 == 0 && (int)threadIdx.x < cnt) {
-            float ws = 0.0f;
+            if (d0 + 16 * NB * w < a.d) {
+                f32x4 acc[NB];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) ws += swsum[buf][threadIdx.x][r];
-            a.part_geom[(voff + cs + threadIdx.x) * PrimRec<SURF>::GP + PrimRec<SURF>::WSLOT] = ws;
-        }
-        if (d0 + 16 * NB * w < a.d) {
-            f32x4 acc[NB];
+                for (int j = 0; j < NB; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int j = 0; j < NB; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int c = TERMS - 1; c >= 0; --c) {      // (small terms first)
 #pragma unroll
-            for (int c = TERMS - 1; c >= 0; --c) {      // (small terms first)
+                    for (int s = 0; s < 8; ++s) {
+                        const bf16x8 av = *reinterpret_cast<const bf16x8*>(sw + (c * CK + xi) * PP + 32 * s + 8 * q);
 #pragma unroll
-                for (int s = 0; s < 8; ++s) {
-                    const bf16x8 av = *reinterpret_cast<const bf16x8*>(sw + (c * CK + xi) * PP + 32 * s + 8 * q);
+                        for (int j = 0; j < NB; ++j)
+                            acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, tg[j][s], acc[j], 0, 0, 0);
+                    }
+                }
 #pragma unroll
-                    for (int j = 0; j < NB; ++j)
-                        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, tg[j][s], acc[j], 0, 0, 0);
+                for (int r = 0; r < 4; ++r) {
+                    const int k = 4 * q + r;
+                    if (k < cnt) {
+                        float* o = a.part_fuse + (voff + cs + k) * a.d + d0 + 16 * NB * w + xi;
+#pragma unroll
+                        for (int j = 0; j < NB; ++j)
+                            if (d0 + 16 * (NB * w + j) + xi < a.d) o[16 * j] = acc[j][r];
+                    }
                 }
             }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int k = 4 * q + r;
-                if (k < cnt) {
-                    float* o = a.part_fuse + (voff + cs + k) * a.d + d0 + 16 * NB * w + xi;
-#pragma unroll
-                    for (int j = 0; j < NB; ++j)
-                        if (d0 + 16 * (NB * w + j) + xi < a.d) o[16 * j] = acc[j][r];
-                }
-            }
+            // No second barrier: the next chunk writes the other buffers, whose last
+            // readers all passed the barrier above.
+            rc = rn;
+            cs = ncs;
         }
-        // No second barrier: the next chunk writes the other buffers, whose last
-        // readers all passed the barrier above.
-        rc = rn;
-        cs = ncs;
+        end -= PARTS ? (int)gridDim.z * len : nt;
+        if (end <= 0) break;
+        first = end > len ? end - len : 0;
+        cs = end - CK > first ? end - CK : first;
+        rc = load_rec<SURF>(a.vrec, at(cs));
     }
 }
 
@@ -447,9 +466,12 @@ void launch_nb(const BwdArgs& a, const ViewTable& vt, int n_tiles, bool ws, hipS
     constexpr int DS = 16 * NB * WAVES;
     const dim3 grid(n_tiles, (a.d + DS - 1) / DS), block(64 * WAVES);
     if (ws)
-        hipLaunchKernelGGL((k_fuse<TERMS, NB, WAVES, true, SURF>), grid, block, 0, s, a, vt, vec);
+        hipLaunchKernelGGL((k_fuse<TERMS, NB, WAVES, true, SURF, false>), grid, block, 0, s, a, vt, vec);
+    else if (TERMS == 2 && a.tseg)
+        hipLaunchKernelGGL((k_fuse<2, NB, WAVES, false, SURF, true>), dim3(grid.x, grid.y, list_parts(n_tiles)), block, 0, s, a,
+                           vt, vec);
     else
-        hipLaunchKernelGGL((k_fuse<TERMS, NB, WAVES, false, SURF>), grid, block, 0, s, a, vt, vec);
+        hipLaunchKernelGGL((k_fuse<TERMS, NB, WAVES, false, SURF, false>), grid, block, 0, s, a, vt, vec);
 }
 
 template <int TERMS, bool SURF>
