@@ -107,9 +107,9 @@ typedef enum { FH_PRIM_GAUSSIAN = 0, FH_PRIM_SURFEL = 1, FH_ENUM_RANGE(FH_PRIM) 
 
 /* Arithmetic form of the compositing kernels. */
 typedef enum {
-    FH_FORM_F32 = 0,        /* FP32 blending; the adjoint and fusion contract FP32 operands on the FP32 matrix unit;
-                               the forward on MFMA with three-term BF16 splits of w and f for FP32 features where d
-                               allows, else on the VALU */
+    FH_FORM_F32 = 0,        /* FP32 blending; contractions of FP32 operands on the FP32 matrix unit, with BF16-stored
+                               features or targets on the BF16 one with the FP32 operand as three BF16 terms (exact);
+                               the forward of FP32 features with three-term splits of w and f where d allows */
     FH_FORM_BF16 = 1,       /* BF16 features, (pixels x K)(K x D) blends on MFMA, FP32 accumulation */
     FH_ENUM_RANGE(FH_FORM)
 } fh_form;

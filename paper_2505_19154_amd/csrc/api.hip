@@ -125,16 +125,17 @@ static fh_status time_calls(Fn f, int reps, hipStream_t s, float* ms) {
 }
 
 // Launch shapes (fh_tuning): defaults and validity.
-// The MFMA forward serves the BF16 form, and the FP32 form with FP32 features
-// at the widths its channel slices divide (the features enter as three BF16
-// terms).  FP32-form runs with BF16-stored features keep the VALU forward: with
-// only the weights split the error would reach ~0.8 of the FP32 rule.
+// render_bf16.hip's forward serves the BF16 form, and the FP32 form with FP32
+// features at the widths its channel slices divide (weights and features enter as
+// three BF16 terms each).  The other runs of the FP32 form take the sequential
+// forward of render_f32.hip: BF16-stored features as stored with exact weights,
+// other FP32 widths on the FP32 matrix unit.
 // float4 per screen record and floats per per-instance partial row
 static int rec_w(const fh_plan* p) { return p->primitive == FH_PRIM_SURFEL ? 4 : 3; }
 static int geom_w(const fh_plan* p) { return p->primitive == FH_PRIM_SURFEL ? 16 : 12; }
 
-// (Surfels take the MFMA forward in the BF16 form only; in the FP32 form they
-// composite on the VALU forward.)
+// (Surfels take render_bf16.hip's forward in the BF16 form only, the sequential one
+// in the FP32 form.)
 static bool mfma_forward(int d, int form, int feat_dtype, int prim) {
     if (prim == FH_PRIM_SURFEL) return form == FH_FORM_BF16;
     return form == FH_FORM_BF16 ||
@@ -188,7 +189,7 @@ static bool same_launch(const fh_plan* p, int which, const fh_tuning& a, const f
     return a.schedule == b.schedule && a.fwd_slice == b.fwd_slice && rows(a) == rows(b);
 }
 
-// The work order of the MFMA walk kernels (fh_tuning.schedule): nullptr for
+// The work order of the walk kernels that take one (fh_tuning.schedule): nullptr for
 // tile index order; else the tiles sorted by cost, longest first (a stable
 // sort of 16-bit keys, ties in index order), cost = the list length
 // (by_range) or the traversal length.

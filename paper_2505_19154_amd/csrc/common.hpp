@@ -32,12 +32,12 @@ enum WsBuf {
     WS_DEPTH_KEY,      // u32 [V*N]
     WS_RECT,           // int4 [V*N]
     WS_ORDER,          // u32 [V*N]  depth-sorted Gaussian index per view
-    WS_ORDER_TMP,      // u32 [V*N]
-    WS_DKEY_TMP,       // u32 [V*N]  radix ping-pong for the depth keys
+    WS_ORDER_TMP,      // u32 [V*N]  of the depth sort; after it [N] the views that visited each Gaussian, a bit a view
+    WS_DKEY_TMP,       // u32 [V*N]  radix ping-pong for the depth keys; after the sort the tiles per rank
     WS_DKEY_TMP2,      // u32 [V*N]
     WS_INST_OFF,       // u32 [V*N + 1] exclusive scan of tiles per rank
     WS_SCAN_TMP,       // u32 scratch for multi-level scans
-    WS_HIST,           // u32 radix histograms
+    WS_HIST,           // u32 digit counts of a sort; between sorts the sums of 1024 ranks' tiles and k_duplicate's first ranks
     WS_RANGES,         // u32 [tiles*2]
     WS_TILE_NITER,     // u32 [tiles]
     WS_TILE_VOFF,      // u32 [tiles+1]
@@ -49,7 +49,7 @@ enum WsBuf {
     WS_VALS_B,         // u32 [cap]
     WS_VSEG,           // u32 [V*N*2] per-rank [start, end) into the rank-sorted visits
     WS_PART_GEOM,      // float [visit_cap * 12]
-    WS_PART_FUSE,      // float [visit_cap * d]
+    WS_PART_FUSE,      // float [visit_cap * d]; in the FP32 form from 256 channels before that f . dF [visits][256]
     WS_VKEY_A,         // u32 [visit_cap] rank of each visited instance (ping-pong)
     WS_VKEY_B,
     WS_VVAL_A,         // u32 [visit_cap] visit index, sorted by rank
@@ -59,7 +59,7 @@ enum WsBuf {
     WS_VGID,           // u32 [visit_cap] Gaussian of each visited instance
     WS_RREC,           // float4 [V*N*3] screen records in depth-rank order
     WS_UNIT_OWNER,     // u32 [unit_cap] long-fusion slot of each unit
-    WS_UPART,          // float [unit_cap * (2 d + 2)] compensated partial sums of each unit
+    WS_UPART,          // float [unit_cap * (2 d + 2)] compensated partial sums of each unit; before them T at segment ends
     WS_PART_NDFD,      // float [visit_cap * 2 * 8] NDFD screen-space partials of the two half-tiles (plan.ndfd)
     WS_NDFD_SC,        // float2 [visit_cap * 256] NDFD (sigma, prefix term) per visited (position, pixel) (plan.ndfd)
     WS_TORDER_KA,      // u32 [tiles] tile schedule: sort keys (ping-pong)

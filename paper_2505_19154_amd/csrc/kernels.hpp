@@ -98,7 +98,7 @@ struct RenderArgs {
     uint32_t* n_iter;
     uint32_t* tile_niter;
     const uint32_t* tile_order;   // nullable: work item i takes tile tile_order[i]
-    int prim;                     // fh_primitive (FP32 VALU kernels)
+    int prim;                     // fh_primitive
 };
 struct BwdArgs {
     const float4* rec;
@@ -206,7 +206,6 @@ void launch_reduce_geom(const ReduceArgs& a, int gp, hipStream_t s);
 void launch_reduce_fuse(const ReduceArgs& a, hipStream_t s);
 // units available for the long fusion reduction at a visit capacity (see reduce.hip)
 int64_t fuse_unit_capacity(int64_t visit_capacity);
-// rw: float4 per record (3, surfels 4)
 // ndfd.hip
 struct NdfdArgs {
     const uint32_t* tile_niter;

@@ -575,7 +575,7 @@ __device__ __forceinline__ bool upstream_zero(const float* grad2d, size_t j) {
 // The outputs are zero-filled before the launch; a Gaussian whose views all
 // pass zero upstream terms (no visited instance reached it) keeps them: every
 // chained term would be zero.  visited: bit v of a Gaussian's word says that
-// view v visited an instance of it (set by the geometry reduction), so the
+// view v visited an instance of it (set by k_vseg), so the
 // others cost four bytes (of 500k Gaussians at 1920x1080 about 2,000 are
 // visited; reading every adjoint row of every view instead took 80 us there and
 // 1.35 ms for 1M Gaussians in 16 views, with the SH arrays in scratch memory).

@@ -36,13 +36,13 @@ __device__ __forceinline__ float hi_f32(uint32_t p) { return __uint_as_float(p &
 
 // One 256-thread workgroup per (tile, slice of 16 NB channels); wave w owns the
 // pixel rows 4 w .. 4 w + 3, one pixel per lane.  The walk is sequential per
-// pixel (the transmittance is the product in list order); the alphas of eight
+// pixel (the transmittance is the product in list order); the alphas of four
 // positions are evaluated ahead of it, so that their latency overlaps.  The
 // weights of 16 positions go to LDS that only this wave reads, and the wave
 // contracts them with the staged features on the FP32 matrix unit,
 //   F[64 px x 16 NB] += W[64 px x 16] . Feat[16 x 16 NB]
-// (v_mfma_f32_16x16x4_f32, FP32 throughout), so a slice of 128 channels walks
-// once where FMAs from LDS took slices of 16 to 64.  Records, Gaussians and
+// (v_mfma_f32_16x16x4_f32; BF16-stored features: FB below), so a slice of 128
+// channels walks once where FMAs from LDS took slices of 16 to 64.  Records, Gaussians and
 // features are staged a chunk of 32 positions at a time, requested one to three
 // chunks ahead (as in render_bf16.hip).  Bound: VALU work of the walk (about 30
 // instructions per pixel and position), then the FP32 matrix rate at 256

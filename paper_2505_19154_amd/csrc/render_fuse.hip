@@ -358,8 +358,7 @@ __global__ __launch_bounds__(1024) void k_fuse_f32(BwdArgs a, ViewTable vt) {
         const int n3 = b3 == 2 ? 0 : b3 + 1, nn3 = n3 == 2 ? 0 : n3 + 1;
         const float4* srec = srecb[b3];
         float* sw = sw2 + b2 * BK * PPF;
-        // the records of the chunk after next, one dword per thread (as in the
-        // gradient kernel)
+        // the records of the chunk after next, one dword per thread
         const int ncs = cs - BK > 0 ? cs - BK : 0;
         const int nncs = ncs - BK > 0 ? ncs - BK : 0;
         const int nncnt = ncs - nncs;

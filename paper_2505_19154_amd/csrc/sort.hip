@@ -779,10 +779,9 @@ void launch_ranks(const RankArgs& a0, uint32_t* hist, uint32_t* scan_tmp, hipStr
 // LDS with their first instance; every rank marks the position where its
 // instances start (the largest rank wins: a rank with no instance starts where
 // the next one does), and a prefix maximum over the range gives every
-// instance its rank.  Every binned rank owns at least one instance, so within
-// one view a range spans at most 2048 ranks and the LDS window holds them;
-// only a range that crosses a view boundary with culled (zero-instance) ranks
-// can need more, and then searches the scan in global memory.
+// instance its rank.  A range that spans more ranks than the window holds (most
+// splats in one tile each, or a view boundary with culled ranks, which own none)
+// searches the scan in global memory, an instance a thread.
 constexpr int DUP_WIN = 1024;
 
 // largest r in [lo, hi] with off[r] <= i (off non-decreasing, off[lo] <= i)
