@@ -18,7 +18,7 @@ from __future__ import annotations
 import torch
 
 from ._lib import FH_FORM_BF16, FhError
-from .raster import FusionAcc, Gaussians, Rasterizer
+from .raster import FusionAcc, Gaussians, Image, Rasterizer
 
 
 class RasterizeFn(torch.autograd.Function):
@@ -30,7 +30,9 @@ class RasterizeFn(torch.autograd.Function):
         ctx.rasterizer = rasterizer
         ctx.generation = rasterizer.generation
         ctx.g = g
-        ctx.img = img
+        # aliases: an output that its own node held would be a cycle, and every pass's images would
+        # stay on the device until the cycle collector runs
+        ctx.img = Image(img.C.detach(), None if img.F is None else img.F.detach(), img.T.detach(), img.n_iter.detach())
         ctx.mark_non_differentiable(img.n_iter)
         F = img.F if img.F is not None else torch.zeros(img.C.shape[0], 0, device=img.C.device)
         return img.C, F, img.T, img.n_iter
